@@ -121,8 +121,8 @@ typedef struct {
  * floor(local_bytes/block_bytes) local blocks and floor(lent_bytes/block_bytes)
  * slice slots, all FREE, lim = n_slice (everything lent), plus the plan
  * upload area of reclaim and run prefetches (16 bytes per block, pinned host
- * and device) and the stream-K attention workspace (partials of one
- * workgroup per compute unit, combine records for 4096 sequences), so that
+ * and device) and the stream-K attention workspace (partials and combine
+ * records of one workgroup per compute unit), so that
  * neither reclaim nor stream-K attention ever allocates.
  * flags: EMA_CREATE_HOST_ONLY (no device memory; copy and attention entry
  * points then take host id arrays, validate them and launch nothing),
@@ -326,7 +326,7 @@ int ema_paged_decode_attention(ema_slice_t h, const void* q, const int32_t* bloc
  * forbid hipMalloc): the same computation, arguments and result as
  * ema_paged_decode_attention, always in the stream-K form, with its partials
  * and combine records in a fixed per-GPU workspace (a file-scope device array
- * of about 8.9 MB, held by each GPU the library runs on until the process
+ * of about 8.5 MB, held by each GPU the library runs on until the process
  * ends) instead of the handle's. The call allocates nothing, on the device or
  * on the host, and never reads device arrays back (on a checked handle it
  * validates nothing on the host; kernels still skip and count invalid ids).

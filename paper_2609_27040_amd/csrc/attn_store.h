@@ -23,4 +23,27 @@ __device__ __forceinline__ void store_out(const AttnArgs& a, int64_t idx, float 
   }
 }
 
+typedef float out_f32x4 __attribute__((ext_vector_type(4)));
+
+// out[idx .. idx + 4) = v (idx a multiple of 4): one store where the output is
+// aligned for it, else one per element.
+__device__ __forceinline__ void store_out4(const AttnArgs& a, int64_t idx, out_f32x4 v) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  if (!a.out_vec) {
+#pragma unroll 1
+    for (int i = 0; i < 4; ++i)
+      store_out(a, idx + i, i == 0 ? v[0] : i == 1 ? v[1] : i == 2 ? v[2] : v[3]);
+  } else if (a.out_dtype == kOutF32) {
+    *reinterpret_cast<out_f32x4*>(static_cast<float*>(a.out) + idx) = v;
+  } else {
+    uint32_t h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      h[i] = a.out_dtype == kOutBF16 ? f32_to_bf16_rne(v[i])
+                                     : __builtin_bit_cast(uint16_t, _Float16(v[i]));
+    *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(a.out) + idx) =
+        u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+  }
+}
+
 }  // namespace ema

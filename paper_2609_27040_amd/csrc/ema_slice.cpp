@@ -4,9 +4,8 @@
 // pools + library scratch, all allocated at create: a kernel error counter, an
 // upload area for the plans and copy lists that reclaim and run prefetches
 // build on the host (with its pinned host staging, sized for the largest
-// plan), and the stream-K attention workspace (partials and combine records
-// for the largest batch the stream-K form takes). Only the grid form of
-// attention (batches above the stream-K limit, or EMA_CREATE_ATTN_GRID) grows
+// plan), and the stream-K attention workspace (partials and combine records of
+// every workgroup). Only the grid form of attention (batches above the stream-K limit, or EMA_CREATE_ATTN_GRID) grows
 // a workspace on first use; growing synchronizes the device.
 #include "ema_slice.h"
 
@@ -45,7 +44,7 @@ struct ema_slice {
   bool d_work_pending = false;
   float* d_part = nullptr;          // stream-K partial slots (fixed size)
   size_t part_cap = 0;              // floats
-  int32_t* d_info = nullptr;        // stream-K: per (sequence, KV head) partial ranges
+  int32_t* d_info = nullptr;        // stream-K: two ints per workgroup
   size_t info_cap = 0;              // ints
   float* d_gpart = nullptr;         // grid form: split-K partials (grows)
   size_t gpart_cap = 0;             // floats
@@ -319,9 +318,10 @@ int ema_slice_create(const ema_kv_shape* shape, size_t local_bytes, size_t lent_
   if (e == hipSuccess) h->h_work_cap = work;
   if (e == hipSuccess) e = hipMalloc(&h->d_work, work * 4);
   if (e == hipSuccess) h->work_cap = work;
-  // Stream-K attention workspace for every head count and the largest batch.
+  // Stream-K attention workspace for every head count: two partial slots and a
+  // combine record per workgroup, whatever the batch.
   const size_t part = size_t(2) * ema::attn_streamk_grid() * ema::kMaxGroup * (ema::kHeadDim + 2);
-  const size_t info = size_t(ema::streamk_max_batch(1)) * shape->num_kv_heads * 3;
+  const size_t info = size_t(2) * ema::attn_streamk_grid();
   if (e == hipSuccess) e = hipMalloc(&h->d_part, part * 4);
   if (e == hipSuccess) h->part_cap = part;
   if (e == hipSuccess) e = hipMalloc(&h->d_info, info * 4);
@@ -765,6 +765,7 @@ int attention_call(ema_slice_t h, const void* q, const int32_t* block_table,
   a.seq_lens = seq_lens;
   a.out = out;
   a.out_dtype = out_dtype;
+  a.out_vec = reinterpret_cast<uintptr_t>(out) % (out_dtype == EMA_F32 ? 16 : 8) == 0;
   a.part_o = part;
   a.part_ml = part ? part + part_rows * ema::kHeadDim : nullptr;
   a.stream_k = stream_k ? 1 : 0;

@@ -88,7 +88,8 @@ struct AttnArgs {
   float* part_o;            // [B][Hq][n_split][128] split-K partial outputs
   float* part_ml;           // [B][Hq][n_split][2] running max (log2 domain) and sum
                             // (stream-K: [2 * grid][G][...] partial slots instead)
-  int32_t* info;            // stream-K: [B][Hkv][3] first / last workgroup, first slot
+  int32_t* info;            // stream-K: [grid][2] pair that begins in a workgroup and goes on
+                            // past it (-1: none), last workgroup that holds it
   int32_t* err_count;
   const char* local;        // local pool base
   int64_t block_bytes;
@@ -97,6 +98,7 @@ struct AttnArgs {
   int32_t chunk;            // tokens per split (grid forms)
   int32_t stream_k;         // matrix-core kernel: stream-K scheduling (else grid form)
   int32_t out_dtype;        // kOutF32, kOutF16 or kOutBF16
+  int32_t out_vec;          // out is aligned for four elements at once
   float scale_log2;         // softmax scale times log2(e)
 };
 
@@ -122,13 +124,13 @@ int attn_streamk_grid();
 // Fixed attention workspace for callers that cannot allocate: a file-scope
 // device array (one per GPU, held until the process ends) with partial slots
 // for up to kNoAllocGrid stream-K workgroups at kMaxGroup query heads per KV
-// head, followed by combine records for kNoAllocPairs (sequence, KV head)
-// pairs. Every call writes each record it reads, so nothing in it needs
-// clearing; calls that overlap on one GPU race on it.
+// head, followed by their combine records. Every call writes each record it
+// reads, so nothing in it needs clearing; calls that overlap on one GPU race on
+// it. The entry point takes up to kNoAllocPairs (sequence, KV head) pairs.
 constexpr int kNoAllocGrid = 512;
 constexpr int kNoAllocPairs = 32768;
 constexpr size_t kNoAllocPartFloats = size_t(2) * kNoAllocGrid * kMaxGroup * (kHeadDim + 2);
-constexpr size_t kNoAllocBytes = kNoAllocPartFloats * 4 + size_t(kNoAllocPairs) * 3 * 4;
+constexpr size_t kNoAllocBytes = kNoAllocPartFloats * 4 + size_t(kNoAllocGrid) * 2 * 4;
 // Device address of that array on the current device (looked up once per
 // device with hipGetSymbolAddress, then cached).
 hipError_t noalloc_workspace(void** ptr);

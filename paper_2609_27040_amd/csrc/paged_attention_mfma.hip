@@ -7,7 +7,8 @@
 // leaves the vector ALUs nearly idle and the kernel bound by HBM.
 //
 // Work is cut into 32-token tiles of one (sequence, KV head). Each wavefront
-// streams tiles with an online softmax, two tiles in flight:
+// streams tiles with an online softmax, the next tile's loads in flight while
+// one is consumed:
 //   scores   S^T[token][head] = K . Q^T   (A = 16 K rows straight from the
 //            block, B = Q^T held in registers; two 16-token tiles whose rows
 //            are chosen so that each lane ends up holding 8 consecutive
@@ -18,20 +19,36 @@
 //            P is split into a 16-bit high part and a 16-bit remainder so the
 //            probabilities keep ~16 significant bits)
 // Scheduling is stream-K: the tiles of all (sequence, KV head) pairs, in that
-// order, are split into equal contiguous ranges, one per workgroup of 4
-// wavefronts and one workgroup per CU, so every CU streams the same bytes
-// whatever the length mix. A workgroup keeps its softmax state across the
-// tiles of one (sequence, KV head) and issues the first loads of its next
-// pair before merging the current one; a pair it covers whole is written out
-// directly, a pair cut by a range boundary leaves one partial per workgroup
-// (unnormalised output, max, sum) that a small combine kernel merges. Merging
-// inside this kernel costs more: partials must cross XCDs, whose L2s are not
+// order, are split into equal contiguous ranges, one per wavefront, four
+// wavefronts to a workgroup and one workgroup per CU, so every CU streams the
+// same bytes whatever the length mix. A wavefront works alone until its range
+// is done: a pair it covers whole it writes out itself, with no barrier; the
+// pieces of pairs cut by range boundaries are merged at the end of the
+// workgroup's range, in LDS within the workgroup, and by a small combine kernel
+// where a pair crosses a workgroup boundary. Merging across workgroups inside
+// this kernel costs more: partials must cross XCDs, whose L2s are not
 // coherent, either behind device-scope fences (a whole-L2 write-back and
 // invalidation per workgroup) or as written-through stores plus an arrival
-// counter, and either way at the end of every workgroup's range. Masked tokens
-// (past the length, or in a block whose id is out of range) get -inf scores
-// and zeroed V, so NaN in unused slots never leaks.
-// Reduction orders depend only on sequence lengths, not on block ids.
+// counter, and either way at the end of every workgroup's range.
+//
+// What bounds it: HBM. Scattered 4 KiB pieces (one head's K or V of a 16-token
+// block at 8 KV heads) read at 6.65 TB/s on this GPU, contiguous memory at
+// 6.9-7.2. An 8B-shaped layer (64 sequences of 1024-4096 tokens, 673 MB) takes
+// 110.6 us (113.4 when the four waves of a workgroup shared one range and met
+// at a barrier after every pair), 512 sequences of 17-1000 tokens (1.07 GB)
+// 179.6 us (230.6, since such ranges also exceeded the lists that were staged
+// in LDS and each pair started from an empty pipeline), a 70B share (211 MB)
+// 42.6 us (43.6). By timestamps in the 8B call: workgroups start over the
+// first 2.3 us (XCDs one after another), have their plan after 0.75 us, the
+// first tile after another 2.5; waves end between 97 and 108 us -- equal bytes
+// at unequal rates, which repeats from call to call only to a third -- and the
+// merge takes 1.6 us. Eight wavefronts to a workgroup: 8B +2 %, 70B share
+// +9 %; waits that let the next tile's loads pass a tile's last use, or not:
+// the same.
+//
+// Masked tokens (past the length, or in a block whose id is out of range) get
+// -inf scores and zeroed V, so NaN in unused slots never leaks. Reduction
+// orders depend only on sequence lengths, not on block ids.
 #include "attn_store.h"
 #include "kernels.h"
 
@@ -51,26 +68,18 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kD = 128;
 constexpr int kWaves = 4;
 constexpr int kThreads = kWaves * 64;
+constexpr int kStreamWaves = 4;            // stream-K form
+constexpr int kStreamThreads = kStreamWaves * 64;
 constexpr int kIt = 32;                    // tokens per tile (one wave iteration)
 constexpr int kPieceTiles = 32;            // tiles whose block ids are staged in LDS at once
 constexpr int kMaxIds = kPieceTiles * kIt / 16;
 constexpr int kGridChunkTiles = 32;        // tiles per workgroup in the grid fallback
-// Each (sequence, KV head) a workgroup touches costs it several tiles' time
-// (the four wavefronts merge and a partial is written; without the staged
-// range below, the tile pipeline also drains and refills); the stream-K split
-// counts it as seg_cost<G>() tiles so that workgroups that touch more pairs
-// get fewer tiles. Measured on 32-token tiles with one workgroup per CU: 8 is
-// best between 6 and 10 at 4 and 8 query heads per KV head; 16 query heads,
-// whose merge and partials are four times larger, do best with 16 (against
-// 8, 12 and 24).
-template <int G>
-constexpr int seg_cost() { return G >= 16 ? 16 : 8; }
-// A stream-K range whose segments and block ids fit these bounds is staged
-// in LDS up front, so each segment can start while the previous one merges.
-constexpr int kMaxSegMax = 8;              // segments of a range (4 for G = 16)
-template <int G>
-constexpr int max_seg() { return G >= 16 ? 4 : kMaxSegMax; }
-constexpr int kRangeIds = 512;             // block ids of a range
+// Every pair a wave touches costs it about a tile's time beyond its tiles (the
+// result goes through LDS, new queries and block ids arrive); the stream-K
+// split counts it as kSegCost tiles. Measured, in us, for 0 / 1 / 2 / 3: an 8B
+// layer 112.1 / 112.0 / 111.8 / 111.4, a 70B share 44.2 / 43.0 / 43.1 / 43.0,
+// 512 sequences of 17-1000 tokens 204 / 181 / 180 / 182.
+constexpr int kSegCost = 2;
 
 __device__ __forceinline__ u32x4 ld16(const char* p) {
   return *reinterpret_cast<const u32x4*>(p);
@@ -163,12 +172,6 @@ __device__ __forceinline__ void consume_tile(Tile& T, const u32x4 (&qb)[4], floa
                                              float& m, float& lsum, f32x4 (&o)[8],
                                              Next&& issue_next) {
   const int nv = T.nv;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {   // branch-free, so waits stay per tile
-    const uint32_t keep = (2 * q < nv ? 0xffffu : 0u) | (2 * q + 1 < nv ? 0xffff0000u : 0u);
-#pragma unroll
-    for (int n = 0; n < 8; ++n) T.v[n][q] &= keep;
-  }
   // Scores for tokens 8q4 + 4t + i of head r16.
   f32x4 s[2];
 #pragma unroll
@@ -177,7 +180,11 @@ __device__ __forceinline__ void consume_tile(Tile& T, const u32x4 (&qb)[4], floa
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) s[t] = mfma<BF16>(T.k[t][kk], qb[kk], s[t]);
   }
+  // The next tile's loads go out here and nowhere else: left to itself the
+  // scheduler sinks them below the first use of this tile's V.
+  __builtin_amdgcn_sched_barrier(0);
   issue_next();
+  __builtin_amdgcn_sched_barrier(0);
   float sv[8];
   float mx = -INFINITY;
 #pragma unroll
@@ -204,6 +211,12 @@ __device__ __forceinline__ void consume_tile(Tile& T, const u32x4 (&qb)[4], floa
   }
   lsum = lsum * alpha + ps;
   m = m_new;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {   // branch-free, so waits stay per tile
+    const uint32_t keep = (2 * q < nv ? 0xffffu : 0u) | (2 * q + 1 < nv ? 0xffff0000u : 0u);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) T.v[n][q] &= keep;
+  }
   const u32x4 PH = {ph[0], ph[1], ph[2], ph[3]};
   const u32x4 PL = {pl[0], pl[1], pl[2], pl[3]};
 #pragma unroll
@@ -321,334 +334,508 @@ __device__ __forceinline__ void attend_segment(const AttnArgs& a, int b, int kvh
   }
 }
 
-// Workgroup-uniform value kept in a scalar register.
+// Wave-uniform value kept in a scalar register.
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
-// One segment of a stream-K range: tiles [j0, j1) of (sequence b, KV head
-// kvh); id0 is the index of its first block id in the range's staged list.
-struct SegDesc {
-  int b, kvh, len, j0, j1, id0;
+// o / l, given inv = 1 / l, one correction step: within an ulp of the division
+// at a fraction of its instructions (l is 1 or more: the row's largest
+// probability is 1). Infinities pass through uncorrected.
+__device__ __forceinline__ float div_by(float o, float l, float inv) {
+  const float q = o * inv;
+  const float c = fmaf(fmaf(-q, l, o), inv, q);
+  return fabsf(q) < INFINITY ? c : q;
+}
+
+// ---- one wavefront's stream of tiles -------------------------------------------------
+//
+// A wavefront streams a list of groups: up to 64 consecutive blocks of one
+// segment, whose ids it holds one per lane. A segment is a run of tiles
+// [j0, j1) of one (sequence, KV head) pair. Everything in Group is uniform
+// over the wave.
+struct Group {
+  int b, kvh, len;
+  int nt;             // tiles of the pair
+  int j0, j1;         // the segment
+  int g0, g1;         // the group's tiles
+  int blk;            // the group's first block
 };
 
-// Q^T of segment s from its LDS copy (rows past G read as zero).
-template <int G>
-__device__ __forceinline__ void load_q(u32x4 (&qb)[4], const uint16_t (*sq)[G][kD], int s, int r16,
-                                       int q4) {
-  const uint16_t* row = sq[s][r16 < G ? r16 : 0] + q4 * 8;
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(row + kk * 32);
-    qb[kk] = r16 < G ? v : u32x4{0, 0, 0, 0};
-  }
+// Whether block g.blk + lane belongs to the group's tiles.
+template <int BS>
+__device__ __forceinline__ bool in_group(const Group& g, int lane) {
+  return (g.blk + lane) * BS < min(g.len, g.g1 * kIt);
 }
 
-// All segments of a stream-K range with their block ids already in LDS: the
-// four waves stream tiles as in attend_segment, and each wave issues the loads
-// of its first tile of the next segment (and the next segment's queries)
-// before the merge of the current one, so no segment starts from an empty
-// pipeline.
-template <int G, int BS, bool BF16, typename Emit>
-__device__ __forceinline__ void attend_range(const AttnArgs& a, const SegDesc* sd, int nseg,
-                                             const int32_t* ids, const uint16_t (*sq)[G][kD],
-                                             Smem<G>& sm, Emit&& emit) {
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
+// Table entry of block g.blk + lane; lanes past the group read its first one.
+// The value is not looked at here, so nothing waits for the load.
+template <int BS>
+__device__ __forceinline__ int32_t load_group_ids(const AttnArgs& a, const Group& g, int lane) {
+  const int j = g.blk + (in_group<BS>(g, lane) ? lane : 0);
+  return a.table[int64_t(g.b) * a.max_blocks + j];
+}
+
+// The group's ids: -1 past its tiles and for ids outside the local pool, which
+// are counted.
+template <int BS>
+__device__ __forceinline__ int32_t check_group_ids(const AttnArgs& a, const Group& g, int lane,
+                                                   int32_t id) {
+  const bool in = in_group<BS>(g, lane);
+  const bool ok = uint32_t(id) < uint32_t(a.n_local);
+  if (in && !ok) atomicAdd(a.err_count, 1);
+  return in && ok ? id : -1;
+}
+
+// Issues the loads of tile j of group g. Block ids come from lane registers,
+// so a block's address is uniform and only the offset inside it is per lane.
+// Lanes whose token lies past the length re-read the tile's first rows (they
+// are masked in consume_tile); a block whose id is out of range reads block 0,
+// which always exists, and is masked too. Without a tile (more == false) the
+// same loads go to a few lines of block 0: every path issues as many loads, so
+// that the waits for the tile before can be counted exactly.
+template <int BS>
+__device__ __forceinline__ void load_tile_ids(Tile& T, const AttnArgs& a, const Group& g, int32_t ids,
+                                              int j, bool more, int r16, int q4) {
+  const int t0 = more ? j * kIt : g.blk * BS;
+  const int lb = t0 / BS - g.blk;
+  const int left = more ? g.len - t0 : 0;
+  const int id0 = more ? __builtin_amdgcn_readlane(ids, lb) : -1;
+  const int64_t Bb = a.block_bytes;
+  const char* base0 = a.local + int64_t(id0 < 0 ? 0 : id0) * Bb;
+  const char* base1 = base0;
+  int id1 = id0;
+  if constexpr (BS == 16) {
+    id1 = more ? __builtin_amdgcn_readlane(ids, lb + 1) : -1;
+    base1 = a.local + int64_t(id1 < 0 ? 0 : id1) * Bb;
+  }
+  const int tb = BS > kIt ? t0 % BS : 0;         // the tile's first token in its block
+  const int khead = (g.kvh * BS + tb) * kD * 2;
+  // K rows: tile t, row r16 -> token t0 + 8*(r16/4) + 4t + r16%4.
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int tok = 8 * (r16 >> 2) + 4 * t + (r16 & 3);
+    const bool in = tok < left;
+    const int row = in ? (BS == 16 ? tok & 15 : tok) : 0;
+    const char* base = (BS == 16 && in && tok >= 16) ? base1 : base0;
+    const char* p = base + (khead + row * kD * 2 + q4 * 16);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) T.k[t][kk] = ld16_stream(p + kk * 64);
+  }
+  // V^T rows: d-tile n, row 16n + r16, tokens t0 + 8q4 .. +8 (one block).
+  const int vt = 8 * q4;
+  const bool vin = vt < left;
+  const bool second = BS == 16 && vin && q4 >= 2;
+  T.nv = !vin || (second ? id1 : id0) < 0 ? 0 : min(left - vt, 8);
+  const int vrow = vin ? r16 * BS + (BS == 16 ? vt & 15 : vt) : 0;
+  const int64_t vhead = Bb / 2 + (g.kvh * kD * BS + tb) * 2;
+  const char* p = (second ? base1 : base0) + vhead + vrow * 2;
+#pragma unroll
+  for (int n = 0; n < 8; ++n) T.v[n] = ld16_stream(p + 16 * n * BS * 2);
+}
+
+// Q^T of one pair as the B operand: lane (head r16, q4) holds channels
+// 32kk + 8q4 .. +8. Lanes past G read head 0 (mask_q zeroes them).
+template <int G>
+__device__ __forceinline__ void load_q(u32x4 (&qn)[4], const AttnArgs& a, int b, int kvh, int r16,
+                                       int q4) {
+  const char* row = reinterpret_cast<const char*>(a.q) +
+                    (int64_t(b) * a.q_heads + kvh * G + (r16 < G ? r16 : 0)) * kD * 2 + q4 * 16;
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) qn[kk] = ld16(row + kk * 64);
+}
+template <int G>
+__device__ __forceinline__ void mask_q(u32x4 (&qb)[4], const u32x4 (&qn)[4], int r16) {
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) qb[kk] = r16 < G ? qn[kk] : u32x4{0, 0, 0, 0};
+}
+
+// Streams the wave's groups, first `g`, then whatever `next` makes of it
+// (next(Group&) -> false when there is no further group), with one tile in
+// flight while another is consumed and the block ids one group ahead. Neither
+// segment ends nor id lists interrupt the loads: the first tile of the next
+// segment and its queries are on their way before the current one is
+// finished. finish(group, flags, m, lsum, o) gets each segment's result
+// (running max and this lane's share of the sum).
+template <int G, int BS, bool BF16, typename Next, typename Finish>
+__device__ __forceinline__ void stream_wave(const AttnArgs& a, Group L, Next&& next,
+                                            Finish&& finish) {
+  const int lane = threadIdx.x & 63;
   const int r16 = lane & 15;
   const int q4 = lane >> 4;
-  const char* pool = a.local;
-  const int64_t Bb = a.block_bytes;
-  auto n_tiles = [&](int s) {
-    const int nt = sd[s].j1 - sd[s].j0;
-    return nt > wave ? (nt - wave + kWaves - 1) / kWaves : 0;
-  };
-  auto load_at = [&](Tile& T, int s, int k) {
-    const int j0 = uniform(sd[s].j0);
-    load_tile<BS>(T, (j0 + wave + k * kWaves) * kIt, uniform(sd[s].len), j0 * kIt / BS,
-                  ids + uniform(sd[s].id0), pool, Bb, uniform(sd[s].kvh), r16, q4);
-  };
-  u32x4 qb[4];
+  Group N = L;
+  int32_t idn = load_group_ids<BS>(a, L, lane);
+  u32x4 qb[4], qn[4];
+  load_q<G>(qn, a, L.b, L.kvh, r16, q4);
+  int32_t ids = check_group_ids<BS>(a, L, lane, idn);
+  int j = L.g0;
   Tile A, B;
-  if (nseg > 0) {
-    load_q<G>(qb, sq, 0, r16, q4);
-    if (n_tiles(0) > 0) load_at(A, 0, 0);
-  }
-  for (int s = 0; s < nseg; ++s) {
-    const int n_it = n_tiles(s);
-    const bool has_next = s + 1 < nseg && n_tiles(s + 1) > 0;
-    bool issued_next = false;
-    float m = -INFINITY;
-    float lsum = 0.0f;
-    f32x4 o[8];
-#pragma unroll
-    for (int n = 0; n < 8; ++n) o[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int it = 0; it < n_it; it += 2) {
-      consume_tile<BF16>(A, qb, a.scale_log2, m, lsum, o, [&] {
-        if (it + 1 < n_it) load_at(B, s, it + 1);
-      });
-      if (it + 1 >= n_it) break;
-      consume_tile<BF16>(B, qb, a.scale_log2, m, lsum, o, [&] {
-        if (it + 2 < n_it) {
-          load_at(A, s, it + 2);
-        } else if (has_next) {
-          load_at(A, s + 1, 0);
-          issued_next = true;
-        }
-      });
-    }
-    if (has_next && !issued_next) load_at(A, s + 1, 0);
-    if (s + 1 < nseg) load_q<G>(qb, sq, s + 1, r16, q4);
+  load_tile_ids<BS>(A, a, L, ids, j, true, r16, q4);
+  mask_q<G>(qb, qn, r16);
+  bool have_next = next(N);
+  idn = load_group_ids<BS>(a, have_next ? N : L, lane);
 
-    // ---- merge the four waves (as in attend_segment) ----
-    __syncthreads();                       // the previous merge is read out
-    lsum += __shfl_xor(lsum, 16);
-    lsum += __shfl_xor(lsum, 32);
-    if (r16 < G) {
-      if (q4 == 0) {
-        sm.m[wave][r16] = m;
-        sm.l[wave][r16] = lsum;
-      }
+  float m = -INFINITY;   // running max of this lane's head (log2 domain)
+  float lsum = 0.0f;     // this lane's share of the running sum
+  f32x4 o[8];
 #pragma unroll
-      for (int n = 0; n < 8; ++n)
-        *reinterpret_cast<f32x4*>(&sm.o[wave][r16][16 * n + 4 * q4]) = o[n];
-    }
-    __syncthreads();
-    for (int e = tid; e < G * kD; e += kThreads) {
-      const int g = e / kD;
-      const int d = e % kD;
-      float M = -INFINITY;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) M = fmaxf(M, sm.m[w][g]);
-      float L = 0.0f, O = 0.0f;
-      if (M != -INFINITY) {
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-          const float mw = sm.m[w][g];
-          if (mw == -INFINITY) continue;
-          const float f = exp2f(mw - M);
-          L = fmaf(f, sm.l[w][g], L);
-          O = fmaf(f, sm.o[w][g][d], O);
+  for (int n = 0; n < 8; ++n) o[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  // Consumes tile X (tile j of group L) while the following one loads into Y.
+  bool more = true;
+  auto turn = [&](Tile& X, Tile& Y) {
+    const Group C = L;
+    const bool last = more && j + 1 == L.j1;
+    consume_tile<BF16>(X, qb, a.scale_log2, m, lsum, o, [&] {
+      if (++j == L.g1) {
+        more = have_next;
+        if (more) {
+          if (last) load_q<G>(qn, a, N.b, N.kvh, r16, q4);
+          ids = check_group_ids<BS>(a, N, lane, idn);
+          L = N;
+          j = L.g0;
+          have_next = next(N);
+          idn = load_group_ids<BS>(a, have_next ? N : L, lane);
         }
       }
-      emit(s, g, d, M, L, O);
+      load_tile_ids<BS>(Y, a, L, ids, j, more, r16, q4);
+    });
+    if (last) {
+      finish(C, m, lsum, o);
+      m = -INFINITY;
+      lsum = 0.0f;
+#pragma unroll
+      for (int n = 0; n < 8; ++n) o[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      mask_q<G>(qb, qn, r16);
     }
+  };
+  // One exit only, every second tile: with a way out between the two turns the
+  // compiler merges it into the loop's back edge, and loads pending there
+  // shorten every wait of the loop. An odd last tile is followed by an empty
+  // one, which changes nothing.
+  do {
+    turn(A, B);
+    turn(B, A);
+  } while (more);
+}
+
+// The segment [j0, j1) of a pair as its first group.
+template <int BS>
+__device__ __forceinline__ void first_group(Group& g) {
+  g.g0 = g.j0;
+  g.blk = g.g0 * kIt / BS;
+  g.g1 = min(g.j1, (g.blk + 64) * BS / kIt);
+}
+
+// The next group of the same segment; false when the segment is done.
+template <int BS>
+__device__ __forceinline__ bool next_in_segment(Group& g) {
+  if (g.g1 >= g.j1) return false;
+  g.g0 = g.g1;
+  g.blk = g.g0 * kIt / BS;
+  g.g1 = min(g.j1, (g.blk + 64) * BS / kIt);
+  return true;
+}
+
+// One partial result (of one segment) in LDS.
+template <int G>
+struct Part {
+  __attribute__((aligned(16))) float o[G][kD];
+  float m[G];
+  float l[G];
+};
+
+template <int G>
+__device__ __forceinline__ void put_part(Part<G>& p, float m, float lsum, const f32x4 (&o)[8],
+                                         int r16, int q4) {
+  lsum += __shfl_xor(lsum, 16);
+  lsum += __shfl_xor(lsum, 32);
+  if (r16 >= G) return;
+  if (q4 == 0) {
+    p.m[r16] = m;
+    p.l[r16] = lsum;
+  }
+#pragma unroll
+  for (int n = 0; n < 8; ++n) *reinterpret_cast<f32x4*>(&p.o[r16][16 * n + 4 * q4]) = o[n];
+}
+
+// Writes channels [4 * d4, 4 * d4 + 4) of output row `row` (sequence and query
+// head) from the merged sum L and unnormalised output O.
+__device__ __forceinline__ void write_row4(const AttnArgs& a, int64_t row, int d4, float L,
+                                           const f32x4& O) {
+  const float inv = 1.0f / L;
+  f32x4 r;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) r[k] = L > 0.0f ? div_by(O[k], L, inv) : 0.0f;
+  store_out4(a, row * kD + 4 * d4, r);
+}
+
+// Writes a whole pair's output from the wave's own partial: the wave reads it
+// back with all 64 lanes (in registers only the lanes of the G heads hold
+// output, and would divide and store it 32 values a lane).
+template <int G>
+__device__ __forceinline__ void write_pair(const AttnArgs& a, int b, int kvh, const Part<G>& p,
+                                           int lane) {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const int64_t row = int64_t(b) * a.q_heads + kvh * G;
+#pragma unroll 1
+  for (int e = lane; e < G * (kD / 4); e += 64) {
+    const int g = e / (kD / 4), d4 = e % (kD / 4);
+    write_row4(a, row + g, d4, p.l[g], *reinterpret_cast<const f32x4*>(&p.o[g][4 * d4]));
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// Merges channels [4 * d4, 4 * d4 + 4) of head g over parts first, second,
+// second + 2, ... (n <= K in all), read in one LDS round trip (indices past n
+// repeat the last part and are given weight 0).
+template <int G, int K>
+__device__ __forceinline__ void merge_parts(const Part<G>* p, int first, int second, int n, int g,
+                                            int d4, float& M, float& L, f32x4& O) {
+  float mm[K], ll[K];
+  f32x4 oo[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = min(k, n - 1);
+    const Part<G>& q = p[i == 0 ? first : second + 2 * (i - 1)];
+    mm[k] = q.m[g];
+    ll[k] = q.l[g];
+    oo[k] = *reinterpret_cast<const f32x4*>(&q.o[g][4 * d4]);
+  }
+  M = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (k >= n) mm[k] = -INFINITY;
+    M = fmaxf(M, mm[k]);
+  }
+  L = 0.0f;
+  O = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (mm[k] == -INFINITY) continue;
+    const float f = exp2f(mm[k] - M);
+    L = fmaf(f, ll[k], L);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) O[c] = fmaf(f, oo[k][c], O[c]);
   }
 }
 
-__device__ __forceinline__ void write_zeros(const AttnArgs& a, int b) {
-  for (int e = threadIdx.x; e < a.q_heads * kD; e += kThreads)
+// Leaves a merged partial in global memory.
+template <int G>
+__device__ __forceinline__ void write_partial4(const AttnArgs& a, int slot, int g, int d4, float M,
+                                               float L, const f32x4& O) {
+  const int64_t row = int64_t(slot) * G + g;
+  *reinterpret_cast<f32x4*>(&a.part_o[row * kD + 4 * d4]) = O;
+  if (d4 == 0) {
+    a.part_ml[row * 2] = M;
+    a.part_ml[row * 2 + 1] = L;
+  }
+}
+
+__device__ __forceinline__ void write_zeros(const AttnArgs& a, int b, int threads) {
+  for (int e = threadIdx.x; e < a.q_heads * kD; e += threads)
     store_out(a, int64_t(b) * a.q_heads * kD + e, 0.0f);
 }
 
-// Stream-K form. Every workgroup reads all lengths once and prefix-sums the
-// unit counts (n_t(b) + kSegCost) * Hkv in LDS (kSegCost = seg_cost<G>());
-// units are ordered (sequence, KV head, unit), each pair's kSegCost cost
-// units (no tiles) ahead of its n_t tiles, and workgroup w takes units
-// [w*per, (w+1)*per), per = ceil(U/grid).
-// For each (sequence, KV head) it touches, it writes the output directly when
-// it holds all of that pair's tiles, else a partial into slot 2w (its first
-// pair) or 2w+1 (its last pair). The workgroup that holds a pair's first tile
-// records (first workgroup, last workgroup, its slot) for the combine. When
-// the range's segments and block ids fit in LDS (kMaxSegMax, kRangeIds), they
-// and the segments' queries are staged once and attend_range carries the
-// tile pipeline across segments; otherwise each segment runs on its own.
+// Inclusive prefix sum over the wave's 64 lanes, by DPP moves: within rows of
+// 16 lanes, then the row totals carried over.
+__device__ __forceinline__ int wave_inclusive_sum(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);    // row_shr 1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // lane 15 of rows 0, 2 to rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // lane 31 to rows 2, 3
+  return x;
+}
+
+// Stream-K form. The units of all (sequence, KV head) pairs, in that order --
+// each pair's kSegCost cost units (no tiles), then its tiles -- are cut into
+// equal contiguous ranges, one per wavefront. A pair that lies within one
+// wave's range is written by that wave; a wave leaves a partial in LDS for a
+// pair it enters in its middle (its head) and for one it leaves unfinished
+// (its tail). One barrier at the end of the workgroup's range, then all four
+// waves merge these: a pair that began and ended within the workgroup is
+// written, one that crosses a workgroup boundary leaves one partial in global
+// memory -- slot 2w for the pair workgroup w entered in its middle, 2w + 1 for
+// the one that begins there and goes on -- and a record (pair, last
+// workgroup), by the workgroup it begins in, for the combine.
 template <int G, int BS, bool BF16>
 // Compiled as if two workgroups shared a CU (at most 256 registers a lane),
 // although one per CU is launched: under the looser bound the compiler's
 // schedule (which then also used accumulation registers) ran every call
 // 11-12 % slower.
-__global__ __launch_bounds__(kThreads, 2) void attn_mfma_streamk(AttnArgs a) {
-  constexpr int kSegCost = seg_cost<G>();
-  __shared__ Smem<G> sm;
+__global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs a) {
   __shared__ int32_t s_len[streamk_max_batch(G)];
-  __shared__ int32_t s_pref[streamk_max_batch(G) + 1];
-  __shared__ int32_t s_seg[kThreads];
+  __shared__ int32_t s_total[kStreamWaves];
+  __shared__ int32_t s_start[kStreamWaves][2];   // first sequence of each wave's range, units into it
+  __shared__ Part<G> s_part[kStreamWaves][2];    // head, tail
+  __shared__ int4 s_open[kStreamWaves];   // head pair (-1: none), whether it ends in this
+                                          // wave; tail pair (-1: none), last workgroup it is in
   const int tid = threadIdx.x;
   const int lane = tid & 63;
+  const int wave = uniform(tid >> 6);
+  const int r16 = lane & 15;
+  const int q4 = lane >> 4;
   const int B = a.batch;
   const int H = a.kv_heads;
-  const int per_t = (B + kThreads - 1) / kThreads;
+
+  // Every workgroup reads all lengths: thread t takes per_t consecutive
+  // sequences, loaded four at a time (one round trip up to 1024 sequences).
+  const int per_t = (B + kStreamThreads - 1) / kStreamThreads;
   const int b0 = min(B, tid * per_t);
   const int b1 = min(B, b0 + per_t);
-  int run = 0;
-  for (int b = b0; b < b1; ++b) {
-    const int raw = a.seq_lens[b];
-    const int len = clamp_len(raw, a);
-    if (blockIdx.x == 0 && len != raw && raw > 0) atomicAdd(a.err_count, 1);
-    s_len[b] = len;
-    s_pref[b] = run;
-    const int nt_b = (len + kIt - 1) / kIt;
-    run += nt_b > 0 ? (nt_b + kSegCost) * H : 0;
-  }
-  s_seg[tid] = run;
-  __syncthreads();
-  if (tid < 64) {   // exclusive scan of the 256 per-thread totals
-    const int v0 = s_seg[4 * lane], v1 = s_seg[4 * lane + 1];
-    const int v2 = s_seg[4 * lane + 2], v3 = s_seg[4 * lane + 3];
-    int sum = v0 + v1 + v2 + v3;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(sum, o);
-      if (lane >= o) sum += t;
-    }
-    const int ex = sum - (v0 + v1 + v2 + v3);
-    s_seg[4 * lane] = ex;
-    s_seg[4 * lane + 1] = ex + v0;
-    s_seg[4 * lane + 2] = ex + v0 + v1;
-    s_seg[4 * lane + 3] = ex + v0 + v1 + v2;
-    if (lane == 63) s_pref[B] = sum;
-  }
-  __syncthreads();
-  for (int b = b0; b < b1; ++b) s_pref[b] += s_seg[tid];
-  __syncthreads();
-  for (int b = blockIdx.x; b < B; b += gridDim.x) {
-    if (s_len[b] != 0) continue;
-    write_zeros(a, b);
-    for (int h = tid; h < H; h += kThreads) {
-      int32_t* info = a.info + (int64_t(b) * H + h) * 3;
-      info[0] = info[1] = info[2] = 0;
-    }
-  }
-
-  const int U = s_pref[B];
-  const int per = (U + int(gridDim.x) - 1) / int(gridDim.x);
-  int u = min(U, int(blockIdx.x) * per);
-  const int u_end = min(U, u + per);
-
-  // The range's segments and all their block ids, staged once.
-  constexpr int kMaxSeg = max_seg<G>();
-  __shared__ SegDesc s_desc[kMaxSeg];
-  __shared__ int32_t s_rids[kRangeIds];
-  __shared__ __attribute__((aligned(16))) uint16_t s_q[kMaxSeg][G][kD];
-  int nseg = 0, nids = 0;
-  {
-    int uu = u;
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (s_pref[mid] <= uu) lo = mid;
-      else hi = mid - 1;
-    }
-    int b = uniform(lo);
-    while (uu < u_end && nseg <= kMaxSeg) {
-      while (uniform(s_pref[b + 1]) <= uu) ++b;
-      const int len = uniform(s_len[b]);
-      const int nt = (len + kIt - 1) / kIt;
-      const int P = nt + kSegCost;
-      const int r = uu - uniform(s_pref[b]);
-      const int kvh = r / P;
-      const int q = r - kvh * P;
-      if (q < kSegCost) {
-        uu += kSegCost - q;
-        continue;
-      }
-      const int j0 = q - kSegCost;
-      const int j1 = min(nt, j0 + (u_end - uu));
-      if (nseg < kMaxSeg && tid == 0) s_desc[nseg] = SegDesc{b, kvh, len, j0, j1, nids};
-      nids += (j1 * kIt - 1) / BS - j0 * kIt / BS + 1;
-      ++nseg;
-      uu += j1 - j0;
-    }
-  }
-  if (nseg <= kMaxSeg && nids <= kRangeIds) {
-    __syncthreads();
-    for (int e = tid; e < nids; e += kThreads) {
-      int sg = 0;
-      while (sg + 1 < nseg && s_desc[sg + 1].id0 <= e) ++sg;
-      const int b = s_desc[sg].b;
-      const int j = s_desc[sg].j0 * kIt / BS + (e - s_desc[sg].id0);
-      int id = -1;
-      if (j * BS < s_desc[sg].len) {
-        id = a.table[int64_t(b) * a.max_blocks + j];
-        if (id < 0 || id >= a.n_local) {
-          atomicAdd(a.err_count, 1);
-          id = -1;
-        }
-      }
-      s_rids[e] = id;
-    }
-    for (int e = tid; e < nseg * G * (kD / 8); e += kThreads) {   // 16-byte pieces of Q rows
-      const int s2 = e / (G * (kD / 8));
-      const int g = (e / (kD / 8)) % G;
-      const int c = e % (kD / 8);
-      const char* src = reinterpret_cast<const char*>(a.q) +
-                        ((int64_t(s_desc[s2].b) * a.q_heads + s_desc[s2].kvh * G + g) * kD + c * 8) * 2;
-      *reinterpret_cast<u32x4*>(&s_q[s2][g][c * 8]) = ld16(src);
-    }
-    __syncthreads();
-    if (tid == 0) {
-      for (int s2 = 0; s2 < nseg; ++s2) {
-        const SegDesc& d = s_desc[s2];
-        if (d.j0 != 0) continue;
-        const int nt = (d.len + kIt - 1) / kIt;
-        int32_t* info = a.info + (int64_t(d.b) * H + d.kvh) * 3;
-        info[0] = int(blockIdx.x);
-        info[1] = (s_pref[d.b] + d.kvh * (nt + kSegCost) + nt + kSegCost - 1) / per;
-        info[2] = s2 == 0 ? 0 : 1;
-      }
-    }
-    attend_range<G, BS, BF16>(a, s_desc, nseg, s_rids, s_q, sm,
-                              [&](int s2, int g, int d, float M, float L, float O) {
-      const SegDesc& sdd = s_desc[s2];
-      const int nt = (sdd.len + kIt - 1) / kIt;
-      if (sdd.j0 == 0 && sdd.j1 == nt) {
-        store_out(a, (int64_t(sdd.b) * a.q_heads + sdd.kvh * G + g) * kD + d, L > 0.0f ? O / L : 0.0f);
-      } else {
-        const int64_t slot = int64_t(blockIdx.x) * 2 + (s2 == 0 ? 0 : 1);
-        a.part_o[(slot * G + g) * kD + d] = O;
-        if (d == 0) {
-          a.part_ml[(slot * G + g) * 2] = M;
-          a.part_ml[(slot * G + g) * 2 + 1] = L;
-        }
-      }
-    });
-    return;
-  }
-
-  int seg = 0;
-  while (u < u_end) {
-    int lo = 0, hi = B - 1;   // last sequence whose first unit is <= u
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (s_pref[mid] <= u) lo = mid;
-      else hi = mid - 1;
-    }
-    const int b = uniform(lo);
-    const int len = uniform(s_len[b]);
+  auto units_of = [&](int len) {
     const int nt = (len + kIt - 1) / kIt;
-    const int P = nt + kSegCost;            // a pair's units: kSegCost, then its tiles
-    const int r = u - uniform(s_pref[b]);
-    const int kvh = r / P;
-    const int q = r - kvh * P;
-    if (q < kSegCost) {                      // cost units carry no tiles
-      u += kSegCost - q;
-      continue;
+    return nt > 0 ? (nt + kSegCost) * H : 0;
+  };
+  int total = 0;
+  for (int c = b0; c < b1; c += 4) {
+    int raw[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) raw[i] = a.seq_lens[min(c + i, b1 - 1)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (c + i >= b1) break;
+      const int len = clamp_len(raw[i], a);
+      if (blockIdx.x == 0 && len != raw[i] && raw[i] > 0) atomicAdd(a.err_count, 1);
+      s_len[c + i] = len;
+      total += units_of(len);
     }
-    const int j0 = q - kSegCost;
-    const int j1 = min(nt, j0 + (u_end - u));
-    const bool whole = j0 == 0 && j1 == nt;
-    const int64_t slot = int64_t(blockIdx.x) * 2 + (seg == 0 ? 0 : 1);
-    attend_segment<G, BS, BF16>(a, b, kvh, len, j0, j1, sm,
-                                [&](int g, int d, float M, float L, float O) {
-      if (whole) {
-        store_out(a, (int64_t(b) * a.q_heads + kvh * G + g) * kD + d, L > 0.0f ? O / L : 0.0f);
-      } else {
-        a.part_o[(slot * G + g) * kD + d] = O;
-        if (d == 0) {
-          a.part_ml[(slot * G + g) * 2] = M;
-          a.part_ml[(slot * G + g) * 2 + 1] = L;
-        }
-      }
-    });
-    if (j0 == 0 && tid == 0) {
-      int32_t* info = a.info + (int64_t(b) * H + kvh) * 3;
-      info[0] = int(blockIdx.x);
-      info[1] = (uniform(s_pref[b]) + kvh * P + P - 1) / per;
-      info[2] = seg == 0 ? 0 : 1;
-    }
-    u += j1 - j0;
-    ++seg;
   }
+  const int incl = wave_inclusive_sum(total);
+  if (lane == 63) s_total[wave] = incl;
+  if (tid < kStreamWaves) s_start[tid][0] = -1;
+  __syncthreads();
+  int before = incl - total, U = 0;
+#pragma unroll
+  for (int w = 0; w < kStreamWaves; ++w) {
+    const int t = s_total[w];
+    if (w < wave) before += t;
+    U += t;
+  }
+  const int n_waves = int(gridDim.x) * kStreamWaves;
+  const int per = (U + n_waves - 1) / n_waves;
+  const int first_wave = int(blockIdx.x) * kStreamWaves;
+  // the thread whose sequences hold a wave's first unit says so
+  for (int b = b0, at = before; b < b1; ++b) {
+    const int n = units_of(s_len[b]);
+#pragma unroll
+    for (int w = 0; w < kStreamWaves; ++w) {
+      const int u = (first_wave + w) * per;
+      if (u >= at && u < at + n) {
+        s_start[w][0] = b;
+        s_start[w][1] = u - at;
+      }
+    }
+    at += n;
+  }
+  __syncthreads();
+
+  int head = -1, head_ends = 0, tail = -1, tail_wg = 0;
+  const int b_first = uniform(s_start[wave][0]);
+  if (b_first >= 0) {
+    const int u0 = (first_wave + wave) * per;
+    const int u1 = min(U, u0 + per);
+    int left = u1 - u0;               // units of the range not yet handed out
+    // The segment starting at unit r of the pair in g (cost units first);
+    // false when the range ends before a tile.
+    auto take = [&](Group& g, int r) {
+      const int cost = max(0, kSegCost - r);
+      if (left <= cost) return false;
+      left -= cost;
+      g.j0 = max(0, r - kSegCost);
+      g.j1 = min(g.nt, g.j0 + left);
+      left -= g.j1 - g.j0;
+      first_group<BS>(g);
+      return true;
+    };
+    auto next_pair = [&](Group& g) {
+      if (left <= kSegCost) return false;
+      if (++g.kvh == H) {
+        g.kvh = 0;
+        do {
+          if (++g.b >= B) return false;
+          g.len = uniform(s_len[g.b]);
+        } while (g.len == 0);
+        g.nt = (g.len + kIt - 1) / kIt;
+      }
+      return take(g, 0);
+    };
+    auto next = [&](Group& g) { return next_in_segment<BS>(g) || next_pair(g); };
+    Group g;
+    g.b = b_first;
+    g.len = uniform(s_len[g.b]);
+    g.nt = (g.len + kIt - 1) / kIt;
+    const int into = uniform(s_start[wave][1]);
+    g.kvh = into / (g.nt + kSegCost);
+    if (take(g, into - g.kvh * (g.nt + kSegCost)))
+      stream_wave<G, BS, BF16>(a, g, next, [&](const Group& c, float m, float lsum,
+                                               const f32x4 (&o)[8]) {
+        const bool begins = c.j0 == 0, ends = c.j1 == c.nt;
+        // the tail's place is free until the range's last segment
+        Part<G>& p = s_part[wave][begins ? 1 : 0];
+        put_part<G>(p, m, lsum, o, r16, q4);
+        if (begins && ends) {
+          write_pair<G>(a, c.b, c.kvh, p, lane);
+          return;
+        }
+        if (begins) {
+          tail = c.b * H + c.kvh;
+          tail_wg = (u1 + (c.nt - c.j1) - 1) / (per * kStreamWaves);   // the range ends with this segment
+        } else {
+          head = c.b * H + c.kvh;
+          head_ends = ends;
+        }
+      });
+  }
+  if (lane == 0) s_open[wave] = int4{head, head_ends, tail, tail_wg};
+  __syncthreads();
+
+  // Chains of LDS partials. All waves together merge the pair that began in an
+  // earlier workgroup, from wave 0's head on; each wave merges the pair that
+  // begins as its tail. A chain goes on through the heads of the following
+  // waves until its pair ends.
+  const int4 mine = s_open[lane % kStreamWaves];
+  const uint32_t ends = uint32_t(__ballot(lane < kStreamWaves && mine.x >= 0 && mine.y != 0));
+  const Part<G>* parts = &s_part[0][0];
+  constexpr int kItems = G * (kD / 4);
+  if (uniform(mine.x) >= 0) {                       // lane 0: wave 0's head
+    const int n = ends ? __builtin_ctz(ends) + 1 : kStreamWaves;
+    for (int e = tid; e < kItems; e += kStreamThreads) {
+      const int g = e / (kD / 4), d4 = e % (kD / 4);
+      float M, L;
+      f32x4 O;
+      merge_parts<G, kStreamWaves>(parts, 0, 2, n, g, d4, M, L, O);
+      write_partial4<G>(a, 2 * blockIdx.x, g, d4, M, L, O);
+    }
+  }
+  if (tail >= 0) {
+    const uint32_t after = ends >> (wave + 1);
+    const int n = 1 + (after ? __builtin_ctz(after) + 1 : kStreamWaves - 1 - wave);
+    const int b = tail / H;
+    const int64_t row = int64_t(b) * a.q_heads + (tail - b * H) * G;
+    for (int e = lane; e < kItems; e += 64) {
+      const int g = e / (kD / 4), d4 = e % (kD / 4);
+      float M, L;
+      f32x4 O;
+      merge_parts<G, kStreamWaves>(parts, 2 * wave + 1, 2 * wave + 2, n, g, d4, M, L, O);
+      if (after)
+        write_row4(a, row + g, d4, L, O);
+      else
+        write_partial4<G>(a, 2 * blockIdx.x + 1, g, d4, M, L, O);
+    }
+  }
+  if (tid < 64) {
+    // the last tail of the workgroup goes on past it if no later head ends
+    const uint64_t tails = __ballot(lane < kStreamWaves && mine.z >= 0);
+    const int w = tails ? 63 - __builtin_clzll(tails) : 0;
+    const bool open = tails && (ends >> (w + 1)) == 0;
+    if (lane == w) {
+      a.info[2 * blockIdx.x] = open ? mine.z : -1;
+      a.info[2 * blockIdx.x + 1] = mine.w;
+    }
+  }
+  for (int b = blockIdx.x; b < B; b += gridDim.x)
+    if (s_len[b] == 0) write_zeros(a, b, kStreamThreads);
 }
 
 // Grid form for batches too large for the LDS work list: grid (chunk of
@@ -665,7 +852,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_mfma_grid(AttnArgs a) {
   if (split == 0 && kvh == 0 && threadIdx.x == 0 && len != raw && raw > 0)
     atomicAdd(a.err_count, 1);
   if (len == 0) {
-    if (split == 0 && kvh == 0) write_zeros(a, b);
+    if (split == 0 && kvh == 0) write_zeros(a, b, kThreads);
     return;
   }
   const int nt = (len + kIt - 1) / kIt;
@@ -688,79 +875,79 @@ __global__ __launch_bounds__(kThreads, 2) void attn_mfma_grid(AttnArgs a) {
   });
 }
 
-// Online merge of partials [0, n) of one output; K loads of each kind per
-// memory round trip, branch-free (indices past n repeat the last partial and
-// are given weight 0), so all K loads are in flight together.
-template <int K>
-__device__ __forceinline__ void merge_partials(const AttnArgs& a, int G, int g, int d, int wa,
-                                               int sa, int n, float& M, float& L, float& O) {
-  for (int j0 = 0; j0 < n; j0 += K) {
-    float mm[K], ll[K], oo[K];
+// Merges the partials of every pair that crosses a stream-K workgroup
+// boundary: one workgroup per stream-K workgroup the pair begins in, one
+// thread per four channels of a head. A pair's first kCombine partials sit at
+// places that need no record (slot 2w + 1, then 2(w + 1), 2(w + 2), ...), so
+// they are loaded along with it and used if the record says so: the kernel is
+// one memory round trip for most pairs. Longer ones go on kCombine at a time.
+constexpr int kCombine = 4;
+template <int G>
+__global__ __launch_bounds__(G * kD / 4 < 64 ? 64 : G * kD / 4) void attn_combine_streamk(
+    AttnArgs a) {
+  const int w0 = blockIdx.x;
+  const int e = threadIdx.x;
+  if (e >= G * (kD / 4)) return;
+  const int g = e / (kD / 4), d4 = e % (kD / 4);
+  const int w_max = int(gridDim.x) - 1;
+  float mm[kCombine], ll[kCombine];
+  f32x4 oo[kCombine];
+  auto load = [&](int i0) {
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const int i = min(j0 + j, n - 1);
-      const int64_t slot = int64_t(wa + i) * 2 + (i == 0 ? sa : 0);
-      mm[j] = a.part_ml[(slot * G + g) * 2];
-      ll[j] = a.part_ml[(slot * G + g) * 2 + 1];
-      oo[j] = a.part_o[(slot * G + g) * kD + d];
+    for (int k = 0; k < kCombine; ++k) {
+      const int64_t slot = 2 * int64_t(min(w0 + i0 + k, w_max)) + (i0 + k == 0 ? 1 : 0);
+      mm[k] = a.part_ml[(slot * G + g) * 2];
+      ll[k] = a.part_ml[(slot * G + g) * 2 + 1];
+      oo[k] = *reinterpret_cast<const f32x4*>(&a.part_o[(slot * G + g) * kD + 4 * d4]);
     }
-#pragma unroll
-    for (int j = 0; j < K; ++j)
-      if (j0 + j >= n) mm[j] = -INFINITY;
+  };
+  load(0);
+  const int pair = a.info[2 * w0], last_wg = a.info[2 * w0 + 1];
+  if (pair < 0) return;
+  const int n = last_wg - w0 + 1;
+  float M = -INFINITY, L = 0.0f;
+  f32x4 O = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int i0 = 0;;) {
     float Mb = M;
 #pragma unroll
-    for (int j = 0; j < K; ++j) Mb = fmaxf(Mb, mm[j]);
-    if (Mb == -INFINITY) continue;
-    const float f_old = M == -INFINITY ? 0.0f : exp2f(M - Mb);
-    L *= f_old;
-    O *= f_old;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const float f = mm[j] == -INFINITY ? 0.0f : exp2f(mm[j] - Mb);
-      L = fmaf(f, ll[j], L);
-      O = fmaf(f, oo[j], O);
+    for (int k = 0; k < kCombine; ++k) {
+      if (i0 + k >= n) mm[k] = -INFINITY;
+      Mb = fmaxf(Mb, mm[k]);
     }
-    M = Mb;
+    if (Mb != -INFINITY) {
+      const float f_old = M == -INFINITY ? 0.0f : exp2f(M - Mb);
+      L *= f_old;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) O[c] *= f_old;
+#pragma unroll
+      for (int k = 0; k < kCombine; ++k) {
+        if (mm[k] == -INFINITY) continue;
+        const float f = exp2f(mm[k] - Mb);
+        L = fmaf(f, ll[k], L);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) O[c] = fmaf(f, oo[k][c], O[c]);
+      }
+      M = Mb;
+    }
+    i0 += kCombine;
+    if (i0 >= n) break;
+    load(i0);
   }
-}
-
-// Merges the partials of every (sequence, KV head) the stream-K ranges cut.
-// Grid (pair, output group): each thread owns one (head, channel) output.
-// info says which workgroups hold the pair's partials (first == last: the
-// pair was written whole, or the sequence is empty).
-__global__ __launch_bounds__(kThreads) void attn_combine_streamk(AttnArgs a) {
   const int H = a.kv_heads;
-  const int G = a.q_heads / H;
-  const int pair = blockIdx.x;
   const int b = pair / H;
-  const int kvh = pair - b * H;
-  const int e = blockIdx.y * kThreads + threadIdx.x;
-  const int32_t* info = a.info + int64_t(pair) * 3;
-  const int wa = info[0], wb = info[1], sa = info[2];
-  if (wb <= wa || e >= G * kD) return;
-  const int g = e / kD;
-  const int d = e % kD;
-  const int n = wb - wa + 1;
-  float M = -INFINITY, L = 0.0f, O = 0.0f;
-  if (n <= 4)
-    merge_partials<4>(a, G, g, d, wa, sa, n, M, L, O);
-  else
-    merge_partials<16>(a, G, g, d, wa, sa, n, M, L, O);
-  store_out(a, (int64_t(b) * a.q_heads + kvh * G + g) * kD + d, L > 0.0f ? O / L : 0.0f);
+  write_row4(a, int64_t(b) * a.q_heads + (pair - b * H) * G + g, d4, L, O);
 }
-
 
 template <int G, int BS, bool BF16>
 hipError_t launch_typed(const AttnArgs& a, hipStream_t stream) {
   if (a.stream_k) {
     const int grid = attn_streamk_grid();
-    hipLaunchKernelGGL((attn_mfma_streamk<G, BS, BF16>), dim3(grid), dim3(kThreads), 0, stream,
-                       a);
+    hipLaunchKernelGGL((attn_mfma_streamk<G, BS, BF16>), dim3(grid), dim3(kStreamThreads), 0,
+                       stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int groups = (a.q_heads / a.kv_heads * kD + kThreads - 1) / kThreads;
-    hipLaunchKernelGGL(attn_combine_streamk, dim3(a.batch * a.kv_heads, groups), dim3(kThreads),
-                       0, stream, a);
+    hipLaunchKernelGGL(attn_combine_streamk<G>, dim3(grid), dim3(std::max(64, G * kD / 4)), 0,
+                       stream, a);
     return hipGetLastError();
   }
   hipLaunchKernelGGL((attn_mfma_grid<G, BS, BF16>), dim3(a.n_split, a.kv_heads, a.batch),

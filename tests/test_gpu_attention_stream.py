@@ -1,0 +1,128 @@
+"""Edges of the stream-K attention's wave-level ranges, against the float64
+oracle: a pair that crosses many workgroups between empty sequences (more
+partials than one combine round reads), pairs of one tile each (several per
+wave, pieces merged within a workgroup), a wave's piece of more than 64 blocks
+(several id lists), tables that hold ids outside the local pool (their tokens
+are left out and counted), and an output that is not aligned for wide stores.
+
+Bar: 2e-3, as for every attention test (16-bit probabilities in two parts,
+fp32 accumulation)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from harness import Workload, oracle_mirror, rel_err
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-3
+
+
+@pytest.fixture(scope="module")
+def ema():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_27040_amd import ema as m
+    return m
+
+
+CASES = {
+    # one pair over every workgroup: 20k tokens, 625 tiles over 1024 waves
+    "one-long": (4, 1, 16, "bf16", [0, 20001, 0]),
+    # 4 heads of one long sequence: each crosses about 64 workgroups
+    "long-16-heads": (64, 4, 32, "f16", [0, 0, 9000, 33]),
+    # one tile a pair, eight pairs a wave and more
+    "short": (16, 8, 16, "f16", [1 + i % 32 for i in range(1500)]),
+    # tiles of one and two blocks, whole and cut
+    "mixed": (8, 2, 64, "bf16", [0, 1, 31, 32, 33, 63, 64, 65, 1023, 1025, 4097, 0]),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_ranges(ema, name):
+    hq, hkv, bs, dtype, lens = CASES[name]
+    print(f"stream {name}", flush=True)
+    cfg = synth.KVConfig("stream", 1, hq, hkv, 128, dtype, bs, len(lens), ("uniform", 0, 0), 0.0,
+                         4100 + len(lens))
+    w = Workload(cfg, lens=lens, staging_slots=1)
+    try:
+        st = oracle_mirror(w)
+        out = w.new_out()
+        out.fill_(float("nan"))
+        w.attention(0, out)
+        again = w.new_out()
+        w.attention(0, again)
+        flat = torch.full((out.numel() + 1,), float("nan"), device="cuda")
+        odd = flat[1:].view(out.shape)                     # 4 bytes past a 16-byte boundary
+        ema.paged_decode_attention(w.h, w.q, w.attn_dev[0], w.lens_dev, odd)
+        torch.cuda.synchronize()
+        assert ema.slice_device_errors(w.h) == 0
+        assert torch.equal(out, again)
+        assert torch.equal(out, odd)
+        ref = oracle.paged_decode_attention(w.q16, w.attn_tables[0], w.lens, st.read_block, w.hkv,
+                                            w.D, w.bs, w.cfg.dtype)
+        assert rel_err(out.cpu().numpy(), ref) <= TOL
+    finally:
+        w.close()
+
+
+def test_several_id_lists_per_wave(ema):
+    """80 sequences of about 4k tokens at 8 KV heads and block size 16: 80 tiles
+    a wave, so its pieces go over several lists of 64 ids, 32 tiles each
+    (sampled sequences against the oracle)."""
+    lens = [4096 - 7 * (i % 5) for i in range(80)]
+    cfg = synth.KVConfig("lists", 1, 32, 8, 128, "bf16", 16, len(lens), ("uniform", 0, 0), 0.0, 4200)
+    w = Workload(cfg, lens=lens, fill="device", staging_slots=1)
+    try:
+        tiles = sum((n + 31) // 32 for n in lens) * w.hkv
+        assert tiles / 1024 > 64 * 16 / 32
+        out = w.new_out()
+        w.attention(0, out)
+        torch.cuda.synchronize()
+        assert ema.slice_device_errors(w.h) == 0
+        got = out.cpu().numpy()
+        for b in (0, 3, 41, 79):
+            ids = torch.as_tensor(w.attn_tables[0][b], device="cuda")
+            rows = w.local_view[ids].cpu().numpy()
+            at = {int(u): r for u, r in zip(w.attn_tables[0][b], rows)}
+            ref = oracle.paged_decode_attention(w.q16[b:b + 1], w.attn_tables[0][b:b + 1],
+                                                w.lens[b:b + 1], at.__getitem__, w.hkv, w.D, w.bs,
+                                                w.cfg.dtype)
+            assert rel_err(got[b:b + 1], ref) <= TOL
+    finally:
+        w.close()
+
+
+@pytest.mark.parametrize("bs", [16, 32, 128])
+def test_ids_outside_the_pool_are_left_out(ema, bs):
+    """Blocks whose id is no local block contribute nothing, and are counted."""
+    lens = [700, 0, 40, 2000]
+    cfg = synth.KVConfig("bad", 1, 8, 2, 128, "bf16", bs, len(lens), ("uniform", 0, 0), 0.0, 4300 + bs)
+    w = Workload(cfg, lens=lens, staging_slots=1)
+    try:
+        st = oracle_mirror(w)
+        tab = w.attn_tables[0].copy()
+        n_total = w.local_view.shape[0]
+        bad = {(0, 1): -1, (0, 2): n_total, (3, 5): 2 ** 31 - 1, (3, 0): -7}
+        for (b, j), u in bad.items():
+            tab[b, j] = u
+        out = w.new_out()
+        w.attention(0, out, table=torch.as_tensor(tab.astype(np.int32), device="cuda"))
+        torch.cuda.synchronize()
+        assert ema.slice_device_errors(w.h) >= len(bad)
+        got = out.cpu().numpy()
+        for b, n in enumerate(lens):
+            keep = [t for t in range(n) if (b, t // bs) not in bad]
+            if not keep:
+                assert (got[b] == 0).all()
+                continue
+            K, V = oracle.attention._gather_sequence(st.read_block, w.attn_tables[0][b], n, w.hkv,
+                                                     w.D, bs)
+            ref = oracle.attention.contiguous_decode_attention(
+                oracle.attention.to_float64(w.q16[b], "bf16"),
+                oracle.attention.to_float64(K[:, keep], "bf16"),
+                oracle.attention.to_float64(V[:, keep], "bf16"))
+            assert rel_err(got[b], ref) <= TOL
+    finally:
+        w.close()
