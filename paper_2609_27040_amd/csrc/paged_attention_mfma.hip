@@ -33,18 +33,18 @@
 //
 // What bounds it: HBM. Scattered 4 KiB pieces (one head's K or V of a 16-token
 // block at 8 KV heads) read at 6.65 TB/s on this GPU, contiguous memory at
-// 6.9-7.2. An 8B-shaped layer (64 sequences of 1024-4096 tokens, 673 MB) takes
-// 110.6 us (113.4 when the four waves of a workgroup shared one range and met
-// at a barrier after every pair), 512 sequences of 17-1000 tokens (1.07 GB)
-// 179.6 us (230.6, since such ranges also exceeded the lists that were staged
-// in LDS and each pair started from an empty pipeline), a 70B share (211 MB)
-// 42.6 us (43.6). By timestamps in the 8B call: workgroups start over the
-// first 2.3 us (XCDs one after another), have their plan after 0.75 us, the
-// first tile after another 2.5; waves end between 97 and 108 us -- equal bytes
-// at unequal rates, which repeats from call to call only to a third -- and the
-// merge takes 1.6 us. Eight wavefronts to a workgroup: 8B +2 %, 70B share
-// +9 %; waits that let the next tile's loads pass a tile's last use, or not:
-// the same.
+// 6.9-7.2. Against workgroups whose four waves shared one range and met at a
+// barrier after every pair (and staged each pair anew where a range did not
+// fit its lists), in us a call: an 8B-shaped layer (64 sequences of 1024-4096
+// tokens, 673 MB) 113.4 -> 109.5, 512 sequences of 17-1000 tokens (1.07 GB)
+// 230 -> 177, a 70B share (211 MB) 43.7 -> 41.5, four of 20-120 thousand tokens
+// 185.5 -> 180; 256 sequences of 17-300 tokens 72.4 -> 39.5. By timestamps in
+// the 8B call: workgroups start over the first 2.3 us (XCDs one after another),
+// have their plan after 0.75 us, the first tile after another 2.5; waves end
+// between 97 and 108 us -- equal bytes at unequal rates, of which only a third
+// repeats from call to call -- and the merge takes 1-1.6 us. Eight wavefronts
+// to a workgroup: 8B +2 %, 70B share +9 %. A loop written so that every wait
+// lets the next tile's loads stay in flight: 8B +2 %, long +2 %.
 //
 // Masked tokens (past the length, or in a block whose id is out of range) get
 // -inf scores and zeroed V, so NaN in unused slots never leaks. Reduction
@@ -180,11 +180,7 @@ __device__ __forceinline__ void consume_tile(Tile& T, const u32x4 (&qb)[4], floa
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) s[t] = mfma<BF16>(T.k[t][kk], qb[kk], s[t]);
   }
-  // The next tile's loads go out here and nowhere else: left to itself the
-  // scheduler sinks them below the first use of this tile's V.
-  __builtin_amdgcn_sched_barrier(0);
   issue_next();
-  __builtin_amdgcn_sched_barrier(0);
   float sv[8];
   float mx = -INFINITY;
 #pragma unroll
@@ -389,22 +385,20 @@ __device__ __forceinline__ int32_t check_group_ids(const AttnArgs& a, const Grou
 // so a block's address is uniform and only the offset inside it is per lane.
 // Lanes whose token lies past the length re-read the tile's first rows (they
 // are masked in consume_tile); a block whose id is out of range reads block 0,
-// which always exists, and is masked too. Without a tile (more == false) the
-// same loads go to a few lines of block 0: every path issues as many loads, so
-// that the waits for the tile before can be counted exactly.
+// which always exists, and is masked too.
 template <int BS>
 __device__ __forceinline__ void load_tile_ids(Tile& T, const AttnArgs& a, const Group& g, int32_t ids,
-                                              int j, bool more, int r16, int q4) {
-  const int t0 = more ? j * kIt : g.blk * BS;
+                                              int j, int r16, int q4) {
+  const int t0 = j * kIt;
   const int lb = t0 / BS - g.blk;
-  const int left = more ? g.len - t0 : 0;
-  const int id0 = more ? __builtin_amdgcn_readlane(ids, lb) : -1;
+  const int left = g.len - t0;
+  const int id0 = __builtin_amdgcn_readlane(ids, lb);
   const int64_t Bb = a.block_bytes;
   const char* base0 = a.local + int64_t(id0 < 0 ? 0 : id0) * Bb;
   const char* base1 = base0;
   int id1 = id0;
   if constexpr (BS == 16) {
-    id1 = more ? __builtin_amdgcn_readlane(ids, lb + 1) : -1;
+    id1 = __builtin_amdgcn_readlane(ids, lb + 1);
     base1 = a.local + int64_t(id1 < 0 ? 0 : id1) * Bb;
   }
   const int tb = BS > kIt ? t0 % BS : 0;         // the tile's first token in its block
@@ -463,13 +457,13 @@ __device__ __forceinline__ void stream_wave(const AttnArgs& a, Group L, Next&& n
   const int q4 = lane >> 4;
   Group N = L;
   int32_t idn = load_group_ids<BS>(a, L, lane);
-  u32x4 qb[4], qn[4];
-  load_q<G>(qn, a, L.b, L.kvh, r16, q4);
+  u32x4 qb[4];
+  Tile A, B;
+  load_q<G>(B.k[0], a, L.b, L.kvh, r16, q4);
   int32_t ids = check_group_ids<BS>(a, L, lane, idn);
   int j = L.g0;
-  Tile A, B;
-  load_tile_ids<BS>(A, a, L, ids, j, true, r16, q4);
-  mask_q<G>(qb, qn, r16);
+  load_tile_ids<BS>(A, a, L, ids, j, r16, q4);
+  mask_q<G>(qb, B.k[0], r16);
   bool have_next = next(N);
   idn = load_group_ids<BS>(a, have_next ? N : L, lane);
 
@@ -483,12 +477,13 @@ __device__ __forceinline__ void stream_wave(const AttnArgs& a, Group L, Next&& n
   bool more = true;
   auto turn = [&](Tile& X, Tile& Y) {
     const Group C = L;
-    const bool last = more && j + 1 == L.j1;
+    const bool last = j + 1 == L.j1;
     consume_tile<BF16>(X, qb, a.scale_log2, m, lsum, o, [&] {
       if (++j == L.g1) {
         more = have_next;
         if (more) {
-          if (last) load_q<G>(qn, a, N.b, N.kvh, r16, q4);
+          // into X's K registers, whose rows have been used
+          if (last) load_q<G>(X.k[0], a, N.b, N.kvh, r16, q4);
           ids = check_group_ids<BS>(a, N, lane, idn);
           L = N;
           j = L.g0;
@@ -496,7 +491,7 @@ __device__ __forceinline__ void stream_wave(const AttnArgs& a, Group L, Next&& n
           idn = load_group_ids<BS>(a, have_next ? N : L, lane);
         }
       }
-      load_tile_ids<BS>(Y, a, L, ids, j, more, r16, q4);
+      if (more) load_tile_ids<BS>(Y, a, L, ids, j, r16, q4);
     });
     if (last) {
       finish(C, m, lsum, o);
@@ -504,17 +499,15 @@ __device__ __forceinline__ void stream_wave(const AttnArgs& a, Group L, Next&& n
       lsum = 0.0f;
 #pragma unroll
       for (int n = 0; n < 8; ++n) o[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      mask_q<G>(qb, qn, r16);
+      mask_q<G>(qb, X.k[0], r16);
     }
   };
-  // One exit only, every second tile: with a way out between the two turns the
-  // compiler merges it into the loop's back edge, and loads pending there
-  // shorten every wait of the loop. An odd last tile is followed by an empty
-  // one, which changes nothing.
-  do {
+  for (;;) {
     turn(A, B);
+    if (!more) break;
     turn(B, A);
-  } while (more);
+    if (!more) break;
+  }
 }
 
 // The segment [j0, j1) of a pair as its first group.
@@ -875,63 +868,75 @@ __global__ __launch_bounds__(kThreads, 2) void attn_mfma_grid(AttnArgs a) {
   });
 }
 
-// Merges the partials of every pair that crosses a stream-K workgroup
-// boundary: one workgroup per stream-K workgroup the pair begins in, one
-// thread per four channels of a head. A pair's first kCombine partials sit at
-// places that need no record (slot 2w + 1, then 2(w + 1), 2(w + 2), ...), so
-// they are loaded along with it and used if the record says so: the kernel is
-// one memory round trip for most pairs. Longer ones go on kCombine at a time.
-constexpr int kCombine = 4;
-template <int G>
-__global__ __launch_bounds__(G * kD / 4 < 64 ? 64 : G * kD / 4) void attn_combine_streamk(
-    AttnArgs a) {
-  const int w0 = blockIdx.x;
-  const int e = threadIdx.x;
-  if (e >= G * (kD / 4)) return;
-  const int g = e / (kD / 4), d4 = e % (kD / 4);
-  const int w_max = int(gridDim.x) - 1;
-  float mm[kCombine], ll[kCombine];
-  f32x4 oo[kCombine];
-  auto load = [&](int i0) {
+// Up to K partials of one pair's head g, channels [4 * d4, 4 * d4 + 4), loaded
+// in one memory round trip: the i0-th on, held by workgroups w0 + i0, ... (the
+// pair's first partial is in its workgroup's slot 2w + 1, the others in 2w).
+template <int G, int K>
+struct Partials {
+  float m[K], l[K];
+  f32x4 o[K];
+  __device__ __forceinline__ void load(const AttnArgs& a, int w0, int i0, int w_max, int g, int d4) {
 #pragma unroll
-    for (int k = 0; k < kCombine; ++k) {
+    for (int k = 0; k < K; ++k) {
       const int64_t slot = 2 * int64_t(min(w0 + i0 + k, w_max)) + (i0 + k == 0 ? 1 : 0);
-      mm[k] = a.part_ml[(slot * G + g) * 2];
-      ll[k] = a.part_ml[(slot * G + g) * 2 + 1];
-      oo[k] = *reinterpret_cast<const f32x4*>(&a.part_o[(slot * G + g) * kD + 4 * d4]);
+      m[k] = a.part_ml[(slot * G + g) * 2];
+      l[k] = a.part_ml[(slot * G + g) * 2 + 1];
+      o[k] = *reinterpret_cast<const f32x4*>(&a.part_o[(slot * G + g) * kD + 4 * d4]);
     }
-  };
-  load(0);
+  }
+  // Merges the first n of them into the running (M, L, O).
+  __device__ __forceinline__ void merge(int n, float& M, float& L, f32x4& O) {
+    float Mb = M;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (k >= n) m[k] = -INFINITY;
+      Mb = fmaxf(Mb, m[k]);
+    }
+    if (Mb == -INFINITY) return;
+    const float f_old = M == -INFINITY ? 0.0f : exp2f(M - Mb);
+    L *= f_old;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) O[c] *= f_old;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (m[k] == -INFINITY) continue;
+      const float f = exp2f(m[k] - Mb);
+      L = fmaf(f, l[k], L);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) O[c] = fmaf(f, o[k][c], O[c]);
+    }
+    M = Mb;
+  }
+};
+
+// Merges the partials of every pair that crosses a stream-K workgroup
+// boundary: grid (stream-K workgroup the pair begins in, heads by two), one
+// wavefront each, one lane per four channels of a head. The record, then up
+// to 4 partials in one round trip, or 16 at a time where a pair has more (one
+// sequence of 30000 tokens over 32 workgroups per head: 30.3 us a call, with
+// 4 at a time 34.5). Loading the first partials along with the record costs
+// more than it saves: most workgroups have no pair to merge, and the call with
+// 16 pairs of 8 heads took 21.2 us instead of 19.6.
+template <int G>
+__global__ __launch_bounds__(64) void attn_combine_streamk(AttnArgs a) {
+  const int w0 = blockIdx.x;
   const int pair = a.info[2 * w0], last_wg = a.info[2 * w0 + 1];
-  if (pair < 0) return;
+  const int e = blockIdx.y * 64 + threadIdx.x;
+  if (pair < 0 || e >= G * (kD / 4)) return;
+  const int g = e / (kD / 4), d4 = e % (kD / 4);
   const int n = last_wg - w0 + 1;
   float M = -INFINITY, L = 0.0f;
   f32x4 O = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int i0 = 0;;) {
-    float Mb = M;
-#pragma unroll
-    for (int k = 0; k < kCombine; ++k) {
-      if (i0 + k >= n) mm[k] = -INFINITY;
-      Mb = fmaxf(Mb, mm[k]);
+  if (n <= 4) {
+    Partials<G, 4> p;
+    p.load(a, w0, 0, last_wg, g, d4);
+    p.merge(n, M, L, O);
+  } else {
+    for (int i0 = 0; i0 < n; i0 += 16) {
+      Partials<G, 16> p;
+      p.load(a, w0, i0, last_wg, g, d4);
+      p.merge(n - i0, M, L, O);
     }
-    if (Mb != -INFINITY) {
-      const float f_old = M == -INFINITY ? 0.0f : exp2f(M - Mb);
-      L *= f_old;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) O[c] *= f_old;
-#pragma unroll
-      for (int k = 0; k < kCombine; ++k) {
-        if (mm[k] == -INFINITY) continue;
-        const float f = exp2f(mm[k] - Mb);
-        L = fmaf(f, ll[k], L);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) O[c] = fmaf(f, oo[k][c], O[c]);
-      }
-      M = Mb;
-    }
-    i0 += kCombine;
-    if (i0 >= n) break;
-    load(i0);
   }
   const int H = a.kv_heads;
   const int b = pair / H;
@@ -946,8 +951,7 @@ hipError_t launch_typed(const AttnArgs& a, hipStream_t stream) {
                        stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_combine_streamk<G>, dim3(grid), dim3(std::max(64, G * kD / 4)), 0,
-                       stream, a);
+    hipLaunchKernelGGL(attn_combine_streamk<G>, dim3(grid, (G + 1) / 2), dim3(64), 0, stream, a);
     return hipGetLastError();
   }
   hipLaunchKernelGGL((attn_mfma_grid<G, BS, BF16>), dim3(a.n_split, a.kv_heads, a.batch),
