@@ -6,24 +6,26 @@
 // block (two wave instructions of 1 KiB each way, fully coalesced; 1, 4, 8
 // and 16 KiB per wavefront move fewer bytes per second). Lists of up to 2^22
 // pieces (8 GiB) of scattered blocks of up to 64 KiB go one wavefront per
-// workgroup, which spreads each block over all XCDs; long ascending runs,
-// larger blocks and larger lists go four wavefronts (8 KiB contiguous) per
-// workgroup, which measured faster or steadier for them.
+// workgroup; long ascending runs, larger blocks and larger lists go four
+// wavefronts (8 KiB contiguous) per workgroup, which measured faster or
+// steadier for them. Either way a block's pieces, up to 256 KiB of them, are
+// dealt to one XCD (see xcd_item).
 //
-// Otherwise the work unit is 4 KiB of one destination block, i.e. 16 tokens x
-// 128 channels of one KV head's K or V -- one block-row at block size 16. One
-// wavefront owns a unit, four per workgroup. Same-layout units are straight
-// copies as above. Units that change layout go through the wave's LDS tile:
-// K rows only change order (256-byte rows are re-addressed, no LDS), V is
+// Otherwise blocks change layout. K rows (256 bytes) only change order, V is
 // transposed between [token][channel] (NHD) and [channel][token] (ATTN) in
 // LDS so that both the global reads and the global writes stay 16 bytes per
-// lane. Into ATTN, a V unit is T = min(BS, 64) tokens of 2048/T channels: its
-// transposed rows are written whole up to 64 tokens (128 B), its token rows
-// are read 64 B or more at a time, and the four units of a workgroup cover
-// whole 256-B token rows; out of ATTN it is 16 tokens of all 128 channels
-// (whole token rows written), or from block size 64 on 32 tokens of 64
-// channels (128-B pieces of token rows written). The tile is dynamic LDS, requested only
-// when the slice layout differs from the local one.
+// lane. From block size 32 on the work unit is a 16 KiB tile per workgroup
+// (block_relayout_kernel): whole 256-byte token rows on the token-major side,
+// whole 64- or 128-byte channel rows on the other. At block size 16, and where
+// the heads do not divide into tiles, it is 4 KiB per wavefront, four per
+// workgroup (block_copy_kernel): 16 tokens (one block's channel rows, which
+// are contiguous) of one head, V through the wave's own LDS tile. Measured,
+// TB/s of read + write, 8 KV heads, lists of 400 MB, 4 KiB units / 16 KiB
+// tiles: into ATTN at block size 16 5.83 / 5.67, 32 5.77 / 5.80, 64 4.55 / 5.70
+// and 256 4.92 / 5.73 (4 KiB units read 64 bytes of a token row there, and
+// wrote the tile eight lanes to an LDS bank); out of ATTN 5.26 / 5.17, 5.11 /
+// 5.46, 4.86 / 5.31 and 4.87 / 5.42. Copies that write scattered blocks stay
+// at 5.2-5.9 in either layout.
 #include "kernels.h"
 
 #include <algorithm>
@@ -35,19 +37,15 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kUnitBytes = 4096;    // work unit of the layout-changing kernel
 constexpr int kPieceBytes = 2048;   // work unit of the same-layout kernel
+constexpr int kTileBytes = 16384;   // work unit of the tiled layout change
+constexpr int64_t kXcdRunBytes = 262144;   // of a block, copied on one XCD
 constexpr int kWaves = 4;
 constexpr int kTileRow = 128 + 8;   // u16 per LDS tile row (padded, keeps 16 B alignment)
 
-// Tokens of one V unit into the local layout: whole transposed rows up to 64
-// tokens (128 B); with larger blocks a unit is 64 tokens x 32 channels, and
-// the four units of a workgroup cover one token group's 128 channels.
-__host__ __device__ constexpr int v_unit_tokens(int bs) { return bs < 64 ? bs : 64; }
-
-// u16 per wave of the relayout tile: 16 x kTileRow or 32 x 72 (out of ATTN),
-// T x (2048/T + 8), T = v_unit_tokens(bs) (into ATTN).
+// u16 per wave of the 4 KiB unit's tile: 16 x kTileRow (out of ATTN, and into
+// it at block size 16), 32 x 72 (into ATTN at block size 32).
 __host__ __device__ constexpr int tile_elems(int bs) {
-  return 16 * kTileRow > 2048 + 8 * v_unit_tokens(bs) ? 16 * kTileRow
-                                                      : 2048 + 8 * v_unit_tokens(bs);
+  return bs > 16 ? 32 * (64 + 8) : 16 * kTileRow;
 }
 
 // Block data is touched once per copy: streaming (non-temporal) loads and
@@ -77,6 +75,23 @@ __device__ __forceinline__ void copy_ids(const CopyIds& c, int32_t i, int32_t& s
     s = c.src[i];
     d = c.dst ? c.dst[i] : c.dst_base + i;
   }
+}
+
+// Work item of workgroup g when `run` consecutive items (of one block) are to
+// stay on one XCD: workgroups go to the 8 XCDs in turn, so within a round of
+// 8 * run items XCD x gets items [x * run, (x + 1) * run). Items from `limit`
+// on (the last, incomplete round) keep their order. A block's pages are then
+// looked up by one XCD's translation caches instead of all eight, and its
+// lines written together: 500 MB lists of scattered blocks, TB/s in order /
+// in runs of up to 256 KiB: swap-in of 64 KiB blocks 6.08 / 6.26, 256 KiB 5.98 /
+// 6.35, 1 MiB 5.94 / 6.33; swap-out of 256 KiB blocks 5.4-5.6 / 6.0, 1 MiB
+// 5.6-5.8 / 6.1; blocks of 16 and 32 KiB the same. Runs of 16-64 KiB gain less.
+__device__ __forceinline__ uint32_t xcd_item(uint32_t g, uint32_t run, uint32_t limit) {
+  if (g >= limit) return g;
+  const uint32_t round = 8 * run;
+  const uint32_t r = g / round;
+  const uint32_t q = g - r * round;
+  return r * round + (q & 7) * run + (q >> 3);
 }
 
 // The table-rewrite share of a reclaim launch: workgroup g rewrites entries
@@ -187,13 +202,11 @@ __global__ __launch_bounds__(256) void block_copy_kernel(PoolView pv, CopyIds id
   const char* sv = sb + half_bytes;
   char* dv = db + half_bytes;
   if (s_nhd) {
-    // NHD -> ATTN, unit (h, token group, channel group): T = v_unit_tokens(BS)
-    // tokens of C = 2048/T channels. Read C channels of each of the T token
-    // rows (LR lanes per row) into the tile as [t][c], then write C
-    // transposed rows of T tokens (LC lanes each): reads and writes stay at
-    // least 64 B contiguous, and the four waves of a workgroup read whole
-    // 256-B token rows between them.
-    const int T = v_unit_tokens(BS);
+    // NHD -> ATTN, unit (h, channel group): all T = BS tokens (16 or 32) of
+    // C = 2048/T channels. Read C channels of each of the T token rows (LR
+    // lanes per row) into the tile as [t][c], then write C transposed rows of
+    // T tokens (LC lanes each).
+    const int T = BS;
     const int C = 2048 / T;
     const int cgs = 128 / C;                  // channel groups per token group
     const int t_base = (tg / cgs) * T;
@@ -223,70 +236,196 @@ __global__ __launch_bounds__(256) void block_copy_kernel(PoolView pv, CopyIds id
       st16(dv + (int64_t(h * 128 + c0 + cc) * BS + t_base + t0) * 2, out);
     }
   } else {
-    // ATTN -> NHD, unit (h, token group, channel group): T = 16 tokens of all
-    // 128 channels, or from block size 64 on T = 32 tokens of 64 channels.
-    // Read the unit's C channel rows of T tokens (T/8 lanes per row), scatter
-    // into the tile as [t][c], then write T token rows of C channels (C/8
-    // lanes per row): whole 256-B token rows at T = 16; at T = 32, 64-B
-    // channel-row reads and 128-B token-row writes (measured faster than
-    // 64 tokens of 32 channels, whose writes are 64 B).
-    const int T = BS >= 64 ? 32 : 16;
-    const int C = 2048 / T;
-    const int cgs = 128 / C;
-    const int t_base = (tg / cgs) * T;
-    const int c0 = (tg % cgs) * C;
-    const int IR = T / 8;                     // 16-B items per channel row
-    const int stride = C + 8;
+    // ATTN -> NHD, unit (h, token group): 16 tokens of all 128 channels. Read
+    // 16 bytes (8 tokens of a channel) per lane, two lanes per channel row;
+    // the lanes of channels 2k and 2k + 1 (lane ^ 2) trade four tokens, so that
+    // each holds both channels of four tokens and scatters them into the
+    // [token][channel] tile as whole words; then write 16 whole 256-B token
+    // rows.
     u32x4 v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int item = j * 64 + lane;
-      const int c = item / IR;
-      const int t0 = (item % IR) * 8;
-      v[j] = ld16(sv + (int64_t(h * 128 + c0 + c) * BS + t_base + t0) * 2);
+      v[j] = ld16(sv + (int64_t(h * 128 + (item >> 1)) * BS + tg * 16 + (item & 1) * 8) * 2);
     }
+    const bool odd = lane & 2;                  // an odd channel
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int item = j * 64 + lane;
-      const int c = item / IR;
-      const int t0 = (item % IR) * 8;
-      const uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+      const int c = (j * 64 + lane) >> 1;
+      const int t0 = (lane & 1) * 8 + (odd ? 4 : 0);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        tw[(t0 + 2 * q) * stride + c] = uint16_t(w[q] & 0xffffu);
-        tw[(t0 + 2 * q + 1) * stride + c] = uint16_t(w[q] >> 16);
+      for (int q = 0; q < 2; ++q) {             // tokens t0 + 2q, t0 + 2q + 1
+        const uint32_t keep = odd ? v[j][2 + q] : v[j][q];
+        const uint32_t give = odd ? v[j][q] : v[j][2 + q];
+        const uint32_t got = __builtin_amdgcn_mov_dpp(int(give), 0x4e, 0xf, 0xf, true);   // lane ^ 2
+        const uint32_t even_c = odd ? got : keep, odd_c = odd ? keep : got;
+        uint32_t* w = reinterpret_cast<uint32_t*>(&tw[(t0 + 2 * q) * kTileRow + (c & ~1)]);
+        w[0] = (even_c & 0xffffu) | (odd_c << 16);
+        w[kTileRow / 2] = (even_c >> 16) | (odd_c & 0xffff0000u);
       }
     }
     wave_lds_sync();
-    const int LW = C / 8;                     // lanes per token row written
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int tl = j * (64 / LW) + lane / LW;
-      const int cp = (lane % LW) * 8;
-      const u32x4 out = *reinterpret_cast<const u32x4*>(&tw[tl * stride + cp]);
-      st16(dv + (int64_t((t_base + tl) * H + h) * 128 + c0 + cp) * 2, out);
+      const int tl = j * 4 + (lane >> 4);
+      const int cp = (lane & 15) * 8;
+      const u32x4 out = *reinterpret_cast<const u32x4*>(&tw[tl * kTileRow + cp]);
+      st16(dv + (int64_t((tg * 16 + tl) * H + h) * 128 + cp) * 2, out);
     }
   }
 }
 
+// Layout change in 16 KiB tiles, one per workgroup: T = min(BS, 64) tokens of
+// 64 / T heads for V, 16 tokens of 4 heads (or fewer heads and more tokens
+// where H is not a multiple of 4) for K, always 64 (token, head) rows of 256
+// bytes. In the token-major layout such a tile is pieces of several adjacent
+// heads per token, in the local layout whole rows.
+template <int T>
+__global__ __launch_bounds__(256) void block_relayout_kernel(PoolView pv, CopyIds ids, int32_t n,
+                                                             int32_t* err_count, TableRewrite rw) {
+  constexpr int kHeads = 64 / T;            // heads of a V tile
+  constexpr int kGroups = T / 8;            // 8-token groups of a tile row
+  __shared__ __attribute__((aligned(16))) uint16_t tile[64 * 128];
+  if (int(blockIdx.x) < rw.n_groups) {
+    rewrite_tables(rw, ids, blockIdx.x);
+    return;
+  }
+  const int tid = threadIdx.x;
+  const int tpb = int(pv.block_bytes / kTileBytes);
+  const int32_t unit = int32_t(blockIdx.x) - rw.n_groups;   // a launch has at most 2^23 tiles
+  if (unit >= n * tpb) return;
+  const int32_t i = unit / tpb;
+  const int k = unit - i * tpb;
+  int32_t s, d;
+  copy_ids(ids, __builtin_amdgcn_readfirstlane(i), s, d);
+  const int32_t n_total = pv.n_local + pv.n_slice;
+  if (s < 0 || s >= n_total || d < 0 || d >= n_total) {
+    if (k == 0 && tid == 0) atomicAdd(err_count, 1);
+    return;
+  }
+  const bool s_local = s < pv.n_local;
+  const bool d_local = d < pv.n_local;
+  const char* sb = s_local ? pv.local + int64_t(s) * pv.block_bytes
+                           : pv.slice + int64_t(s - pv.n_local) * pv.block_bytes;
+  char* db = d_local ? pv.local + int64_t(d) * pv.block_bytes
+                     : pv.slice + int64_t(d - pv.n_local) * pv.block_bytes;
+  u32x4 v[4];
+  if (s_local == d_local) {                 // same layout: a straight copy
+    const int64_t off = int64_t(k) * kTileBytes + tid * 16;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = ld16(sb + off + j * 4096);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) st16(db + off + j * 4096, v[j]);
+    return;
+  }
+  const int H = pv.kv_heads;
+  const int BS = pv.block_size;
+  const int half_tiles = tpb / 2;
+  const int64_t half_bytes = pv.block_bytes / 2;
+  if (k < half_tiles) {
+    // K: 256-byte rows change order only; row (h, t) is row h*BS + t of the
+    // local layout and t*H + h of the token-major one
+    const int hk = H % 4 == 0 ? 4 : H % 2 == 0 ? 2 : 1;
+    const int tk = 64 / hk < BS ? 64 / hk : BS;
+    const int hg = 64 / tk;
+    const int tgs = BS / tk;
+    const int h0 = (k / tgs) * hg;
+    const int t0 = (k % tgs) * tk;
+    int64_t nhd[4], att[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int row = j * 16 + (tid >> 4);
+      const int t = t0 + row / hg, h = h0 + row % hg;
+      nhd[j] = (int64_t(t) * H + h) * 256 + (tid & 15) * 16;
+      att[j] = (int64_t(h) * BS + t) * 256 + (tid & 15) * 16;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = ld16(sb + (s_local ? att[j] : nhd[j]));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) st16(db + (d_local ? att[j] : nhd[j]), v[j]);
+    return;
+  }
+  // V: transposed between [token][channel] and [channel][token] in LDS. The
+  // tile holds 16-byte pieces (8 channels) of row (head, token); piece p of
+  // token t sits at p ^ swizzle(t), so that lanes which differ in their
+  // 8-token group reach different banks.
+  const int tgs = BS / T;
+  const int kv = k - half_tiles;
+  const int h0 = (kv / tgs) * kHeads;
+  const int t0 = (kv % tgs) * T;
+  auto at = [](int hh, int t, int c) {      // element of the tile
+    const int sw = (t >> 3) * (8 / kGroups);
+    return (hh * T + t) * 128 + ((((c >> 3) ^ sw) << 3) | (c & 7));
+  };
+  int64_t nhd[4], att[4];
+  int row_h[4], row_t[4], col_h[4], col_c[4], col_t[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int row = j * 16 + (tid >> 4);    // token-major side: 16 lanes per row
+    row_t[j] = row / kHeads;
+    row_h[j] = row % kHeads;
+    nhd[j] = half_bytes + (int64_t(t0 + row_t[j]) * H + h0 + row_h[j]) * 256 + (tid & 15) * 16;
+    const int item = j * 256 + tid;         // local side: kGroups lanes per channel
+    col_t[j] = (item % kGroups) * 8;
+    col_c[j] = (item / kGroups) % 128;
+    col_h[j] = item / (kGroups * 128);
+    att[j] = half_bytes + (int64_t((h0 + col_h[j]) * 128 + col_c[j]) * BS + t0 + col_t[j]) * 2;
+  }
+  if (d_local) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = ld16(sb + nhd[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *reinterpret_cast<u32x4*>(&tile[at(row_h[j], row_t[j], (tid & 15) * 8)]) = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint32_t w[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        w[q] = uint32_t(tile[at(col_h[j], col_t[j] + 2 * q, col_c[j])]) |
+               (uint32_t(tile[at(col_h[j], col_t[j] + 2 * q + 1, col_c[j])]) << 16);
+      st16(db + att[j], u32x4{w[0], w[1], w[2], w[3]});
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = ld16(sb + att[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        tile[at(col_h[j], col_t[j] + 2 * q, col_c[j])] = uint16_t(w[q] & 0xffffu);
+        tile[at(col_h[j], col_t[j] + 2 * q + 1, col_c[j])] = uint16_t(w[q] >> 16);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      st16(db + nhd[j], *reinterpret_cast<const u32x4*>(&tile[at(row_h[j], row_t[j], (tid & 15) * 8)]));
+  }
+}
+
 // Same-layout copy (both pools in the local layout): wave w of workgroup g
-// (blockDim.x / 64 waves each) moves piece g * (blockDim.x / 64) + w, 2 KiB of
-// block src_ids[i] to the same offset of block dst_ids[i]. Out-of-range ids
-// are skipped and counted once per block.
+// moves piece xcd_item(g) * kWaves + w, 2 KiB of block src_ids[i], to the same
+// offset of block dst_ids[i].
+// Out-of-range ids are skipped and counted once per block.
 __global__ __launch_bounds__(256) void block_copy_same_kernel(PoolView pv, CopyIds ids,
                                                               int32_t n, int32_t* err_count,
-                                                              TableRewrite rw) {
+                                                              TableRewrite rw, uint32_t xcd_run,
+                                                              uint32_t xcd_limit) {
   if (int(blockIdx.x) < rw.n_groups) {
     rewrite_tables(rw, ids, blockIdx.x);
     return;
   }
   const int lane = threadIdx.x & 63;
-  const int ppb = int(pv.block_bytes / kPieceBytes);
-  const int64_t piece =
-      (int64_t(blockIdx.x) - rw.n_groups) * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (piece >= int64_t(n) * ppb) return;
+  const uint32_t ppb = uint32_t(pv.block_bytes / kPieceBytes);
+  // a launch has at most 2^25 wavefronts: pieces fit in 32 bits
+  const uint32_t piece = xcd_item(blockIdx.x - rw.n_groups, xcd_run, xcd_limit) * kWaves +
+                         (threadIdx.x >> 6);
+  if (piece >= uint32_t(n) * ppb) return;
   const int32_t i = int32_t(piece / ppb);
-  const int k = int(piece - int64_t(i) * ppb);
+  const int k = int(piece - uint32_t(i) * ppb);
   int32_t s, d;
   copy_ids(ids, __builtin_amdgcn_readfirstlane(i), s, d);
   const int32_t n_total = pv.n_local + pv.n_slice;
@@ -303,6 +442,38 @@ __global__ __launch_bounds__(256) void block_copy_same_kernel(PoolView pv, CopyI
   const u32x4 v1 = ld16(sb + off + 1024);
   st16(db + off, v0);
   st16(db + off + 1024, v1);
+}
+
+// Same-layout copy of a list of scattered blocks, one wavefront per workgroup:
+// workgroup (k, y, z) moves 2 KiB piece k of block z * kListRows + y. The grid
+// gives piece and block, so nothing is divided, and the few arguments come in
+// one load: a wavefront lives only for its ids, its two loads and its two
+// stores, and how long it lives sets how many bytes a CU keeps in flight.
+// 9801 blocks of 64 KiB take 207.7 us (6.18 TB/s); with one more division and
+// the general kernel's arguments 209.6, with four wavefronts to a workgroup
+// 6.02 TB/s.
+constexpr int kListRows = 32768;
+__global__ __launch_bounds__(64) void block_copy_list_kernel(
+    char* local, char* slice, const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+    int64_t block_bytes, int32_t n_local, int32_t n_total, int32_t n, int32_t* err_count) {
+  const int32_t i = int32_t(blockIdx.z) * kListRows + int32_t(blockIdx.y);
+  if (i >= n) return;
+  const int32_t s = src[i];
+  const int32_t d = dst[i];
+  const int lane = threadIdx.x;
+  if (uint32_t(s) >= uint32_t(n_total) || uint32_t(d) >= uint32_t(n_total)) {
+    if (blockIdx.x == 0 && lane == 0) atomicAdd(err_count, 1);
+    return;
+  }
+  const int64_t off = int64_t(blockIdx.x) * kPieceBytes + lane * 16;
+  const char* sp = (s < n_local ? local + int64_t(s) * block_bytes
+                                : slice + int64_t(s - n_local) * block_bytes) + off;
+  char* dp = (d < n_local ? local + int64_t(d) * block_bytes
+                          : slice + int64_t(d - n_local) * block_bytes) + off;
+  const u32x4 v0 = ld16(sp);
+  const u32x4 v1 = ld16(sp + 1024);
+  st16(dp, v0);
+  st16(dp + 1024, v1);
 }
 
 // One workgroup per (sequence, KV head), one thread per channel: the K element
@@ -347,11 +518,21 @@ hipError_t launch_copy(const PoolView& pv, CopyIds ids, int32_t n, int32_t* err_
   }
   if (n <= 0 && rwl.n_groups == 0) return hipSuccess;
   const bool same = pv.slice_layout == 0;
+  // Tiles are min(BS, 64) tokens of whole groups of heads; block size 16 does
+  // better in 4 KiB units.
+  const bool tiled = !same && pv.block_size >= 32 && (pv.block_size >= 64 || pv.kv_heads % 2 == 0);
   const int64_t upb = pv.block_bytes / (same ? kPieceBytes : kUnitBytes);   // waves per block
-  const int wg_waves =
-      same && !runs && pv.block_bytes <= 65536 && int64_t(n) * upb <= (int64_t(1) << 22) ? 1
-                                                                                        : kWaves;
-  const size_t lds = same ? 0 : size_t(kWaves) * tile_elems(pv.block_size) * 2;
+  // scattered lists of blocks of up to 64 KiB, at most 2^22 pieces
+  if (same && !runs && rwl.n_groups == 0 && ids.n_runs == 0 && ids.dst && pv.block_bytes <= 65536 &&
+      int64_t(n) * upb <= (int64_t(1) << 22)) {
+    const unsigned rows = unsigned(std::min(n, kListRows));
+    hipLaunchKernelGGL(block_copy_list_kernel,
+                       dim3(unsigned(upb), rows, unsigned((n + kListRows - 1) / kListRows)),
+                       dim3(64), 0, stream, pv.local, pv.slice, ids.src, ids.dst, pv.block_bytes,
+                       pv.n_local, pv.n_local + pv.n_slice, n, err_count);
+    return hipGetLastError();
+  }
+  const size_t lds = same || tiled ? 0 : size_t(kWaves) * tile_elems(pv.block_size) * 2;
   // A launch stays below 2^32 work-items: at most 2^25 wavefronts. The table
   // rewrite rides on the first launch; lists are split, run plans always fit.
   const int64_t max_blocks = std::max<int64_t>(1, (int64_t(1) << 25) / upb);
@@ -359,20 +540,31 @@ hipError_t launch_copy(const PoolView& pv, CopyIds ids, int32_t n, int32_t* err_
   int64_t b0 = 0;
   do {
     const int32_t m = int32_t(std::max<int64_t>(0, std::min<int64_t>(max_blocks, n - b0)));
-    const int64_t grid = (int64_t(m) * upb + wg_waves - 1) / wg_waves + rwl.n_groups;
-    const unsigned threads = same ? unsigned(64 * wg_waves) : 256u;
+    const int64_t grid = (int64_t(m) * upb + kWaves - 1) / kWaves + rwl.n_groups;
     CopyIds part = ids;
     if (ids.n_runs == 0) {
       part.src = m ? ids.src + b0 : nullptr;
       part.dst = m && ids.dst ? ids.dst + b0 : nullptr;
       part.dst_base = ids.dst ? 0 : int32_t(ids.dst_base + b0);
     }
-    if (same)
-      hipLaunchKernelGGL(block_copy_same_kernel, dim3(unsigned(grid)), dim3(threads), 0, stream,
-                         pv, part, m, err_count, rwl);
-    else
-      hipLaunchKernelGGL(block_copy_kernel, dim3(unsigned(grid)), dim3(threads), lds, stream, pv,
+    if (same) {
+      // whole workgroups of a block, up to 256 KiB, to an XCD; full rounds only
+      const int64_t groups = int64_t(m) * upb / kWaves;
+      const uint32_t run = uint32_t(std::min(upb, kXcdRunBytes / kPieceBytes) / kWaves);
+      const uint32_t limit = pv.block_bytes <= 65536
+                                 ? 0
+                                 : uint32_t(groups / (8 * int64_t(run)) * (8 * int64_t(run)));
+      hipLaunchKernelGGL(block_copy_same_kernel, dim3(unsigned(grid)), dim3(256), 0, stream,
+                         pv, part, m, err_count, rwl, run, limit);
+    } else if (tiled) {
+      hipLaunchKernelGGL(pv.block_size >= 64 ? block_relayout_kernel<64>
+                                             : block_relayout_kernel<32>,
+                         dim3(unsigned(grid)), dim3(256), 0, stream, pv, part, m, err_count,
+                         rwl);
+    } else {
+      hipLaunchKernelGGL(block_copy_kernel, dim3(unsigned(grid)), dim3(256), lds, stream, pv,
                          part, m, err_count, rwl);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     rwl.n_groups = 0;
