@@ -174,6 +174,14 @@ int grow_device(void** p, size_t* cap, size_t need, size_t elem, hipStream_t st)
   return EMA_OK;
 }
 
+// An event that only orders later device work behind kernels that read a list
+// (the next upload must not overwrite it under them). It makes nothing visible
+// to the host, so its marker needs no system-scope fence: the marker behind a
+// swap of two-layer groups takes 3.8 us of the stream instead of 5.6.
+hipError_t create_use_event(hipEvent_t* ev) {
+  return hipEventCreateWithFlags(ev, hipEventDisableTiming | hipEventDisableSystemFence);
+}
+
 void release(ema_slice* h) {
   if (!h->host_only) {
     (void)hipDeviceSynchronize();
@@ -309,7 +317,7 @@ int ema_slice_create(const ema_kv_shape* shape, size_t local_bytes, size_t lent_
   if (e == hipSuccess) e = hipMalloc(&h->d_err, 4);
   if (e == hipSuccess) e = hipMemset(h->d_err, 0, 4);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->h_work_ev, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&h->d_work_ev, hipEventDisableTiming);
+  if (e == hipSuccess) e = create_use_event(&h->d_work_ev);
   // Reclaim's plan upload (movers' sources and destinations, the returned
   // range's remap, the released blocks outside it: at most 4 ints per block)
   // and run prefetches' block lists (2 per block), so neither ever allocates.
@@ -835,7 +843,7 @@ int ema_slab_init(ema_slice_t h, const ema_slab_cfg* cfg) try {
     e = hipMalloc(&h->d_slab, cap * 4);
     if (e == hipSuccess) e = hipHostMalloc(&h->h_slab, cap * 4, hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->slab_up_ev, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&h->slab_use_ev, hipEventDisableTiming);
+    if (e == hipSuccess) e = create_use_event(&h->slab_use_ev);
     if (e != hipSuccess) return hip_fail(e, "slab_init");
     h->slab_cap = cap;
   }
