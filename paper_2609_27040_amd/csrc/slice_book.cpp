@@ -124,15 +124,47 @@ int SliceBook::alloc(int32_t pool, int32_t n, const int32_t* owners, int32_t* ou
   return kOk;
 }
 
+// ---------------------------------------------------------------- IdSet --
+// A set of up to n block ids: a bitmap over the pools, and a hash set for ids
+// outside them (which the callers refuse anyway) and for few ids of large
+// pools, where clearing the bitmap would take longer (a word clears about 16
+// times faster than an id hashes). Freeing the 1300 blocks of a reclaim took
+// 40 us with the hash set alone, 3 with the bitmap.
+namespace {
+class IdSet {
+ public:
+  IdSet(int32_t n_total, int32_t n) : n_(n_total / 64 <= 16LL * n ? uint32_t(n_total) : 0u) {
+    w_.assign((size_t(n_) + 63) / 64, 0);
+    if (n_ == 0) other_.reserve(size_t(n) * 2);
+  }
+  bool contains(int32_t u) const {
+    if (uint32_t(u) < n_) return (w_[uint32_t(u) >> 6] >> (u & 63)) & 1;
+    return other_.count(u) != 0;
+  }
+  bool insert(int32_t u) {   // false if it was in already
+    if (uint32_t(u) >= n_) return other_.insert(u).second;
+    uint64_t& w = w_[uint32_t(u) >> 6];
+    const uint64_t bit = 1ull << (u & 63);
+    const bool fresh = (w & bit) == 0;
+    w |= bit;
+    return fresh;
+  }
+
+ private:
+  uint32_t n_;
+  std::vector<uint64_t> w_;
+  std::unordered_set<int32_t> other_;
+};
+}  // namespace
+
 int SliceBook::free_blocks(const int32_t* ids, int32_t n, std::string* err) {
   if (n < 0 || (n > 0 && !ids)) {
     *err = "free: n < 0 or NULL array";
     return kErrInval;
   }
-  std::unordered_set<int32_t> seen;
-  seen.reserve(size_t(n) * 2);
+  IdSet seen(n_local_ + n_slice_, n);
   for (int32_t i = 0; i < n; ++i)
-    if (!seen.insert(ids[i]).second) {
+    if (!seen.insert(ids[i])) {
       *err = "free: duplicate id";
       return kErrInval;
     }
@@ -185,15 +217,14 @@ int SliceBook::check_pairs(const int32_t* src, const int32_t* dst, int32_t n,
     *err = "copy list: n < 0 or NULL array";
     return kErrInval;
   }
-  std::unordered_set<int32_t> d;
-  d.reserve(size_t(n) * 2);
+  IdSet d(n_local_ + n_slice_, n);
   for (int32_t i = 0; i < n; ++i)
-    if (!d.insert(dst[i]).second) {
+    if (!d.insert(dst[i])) {
       *err = "copy list: duplicate destination";
       return kErrInval;
     }
   for (int32_t i = 0; i < n; ++i)
-    if (d.count(src[i])) {
+    if (d.contains(src[i])) {
       *err = "copy list: source and destination overlap";
       return kErrInval;
     }

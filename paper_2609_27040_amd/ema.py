@@ -127,9 +127,40 @@ def _check(rc):
         raise EmaError(rc, _lib.ema_last_error().decode())
 
 
-# Per handle: host-only flag, 16-bit dtype and KV heads, recorded at create,
-# so that the checks below need no library call.
+# Per handle: host-only flag, 16-bit dtype, KV heads and blocks of both pools,
+# recorded at create, so that the checks below need no library call.
 _HANDLES = {}
+
+
+class _Torch:
+    """What the marshalling needs of torch, looked up once and on first use
+    (host-only slices do not need torch): every call of a decode step passes
+    here, and on small calls the host part is most of the time."""
+
+    def __init__(self):
+        import torch
+        self.Tensor = torch.Tensor
+        self.out_codes = {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}
+        self.out_types = tuple(self.out_codes)
+        self.i32 = (torch.int32,)
+        self.kv16 = {F16: (torch.float16,), BF16: (torch.bfloat16,)}
+        self.any16 = (torch.float16, torch.bfloat16, torch.int16)
+        raw, dev = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream",
+                                                         "_cuda_getDevice"))
+        if raw and dev:
+            self.stream = lambda: raw(dev())
+        else:
+            self.stream = lambda: torch.cuda.current_stream().cuda_stream
+
+
+_TORCH = None
+
+
+def _torch():
+    global _TORCH
+    if _TORCH is None:
+        _TORCH = _Torch()
+    return _TORCH
 
 
 def _host_only(h):
@@ -145,10 +176,10 @@ def _bad(msg):
 
 def _dev(t, name, dtypes, numel=0):
     """A device-array argument: a contiguous torch tensor on the GPU of one of
-    ``dtypes`` with at least ``numel`` elements. The kernels read whatever the
-    pointer addresses, so a host array or a short tensor is refused here."""
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    ``dtypes`` with at least ``numel`` elements; returns its address. The
+    kernels read whatever the pointer addresses, so a host array or a short
+    tensor is refused here."""
+    if not isinstance(t, _torch().Tensor) or not t.is_cuda:
         _bad(f"{name}: expected a GPU tensor, got {type(t).__name__}")
     if t.dtype not in dtypes:
         _bad(f"{name}: dtype {t.dtype} not in {dtypes}")
@@ -156,30 +187,24 @@ def _dev(t, name, dtypes, numel=0):
         _bad(f"{name}: not contiguous")
     if t.numel() < numel:
         _bad(f"{name}: {t.numel()} elements, {numel} needed")
-    return t
+    return t.data_ptr()
 
 
 def _i32_dev(t, name, numel=0):
-    import torch
-    return _dev(t, name, (torch.int32,), numel)
+    return _dev(t, name, _torch().i32, numel)
 
 
-def _kv16_dev(h, t, name, numel):
-    """16-bit K/V/query data; when the handle's dtype is known, it must match."""
-    import torch
-    rec = _HANDLES.get(h)
-    want = {F16: (torch.float16,), BF16: (torch.bfloat16,)}.get(rec[1]) if rec else None
-    return _dev(t, name, want or (torch.float16, torch.bfloat16, torch.int16), numel)
+def _kv16_types(rec):
+    """16-bit K/V/query types; when the handle's dtype is known, it must match."""
+    T = _torch()
+    return T.kv16.get(rec[1], T.any16) if rec else T.any16
 
 
-def _ids(h, a, n, name):
-    """Id list: host int32 array for a host-only slice, else a GPU int32 tensor."""
-    if _host_only(h):
-        a = _i32_host(a)
-        if len(a) < n:
-            _bad(f"{name}: {len(a)} ids, {n} needed")
-        return a
-    return _i32_dev(a, name, n)
+def _host_ids(a, n, name):
+    a = _i32_host(a)
+    if len(a) < n:
+        _bad(f"{name}: {len(a)} ids, {n} needed")
+    return a
 
 
 def _ptr(x):
@@ -197,8 +222,7 @@ def _i32_host(a):
 
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _torch().stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -214,7 +238,9 @@ def slice_create(num_kv_heads, head_dim, block_size, dtype, slice_layout, local_
              | (CREATE_ATTN_GRID if attn_grid else 0))
     _check(_lib.ema_slice_create(ctypes.byref(shape), int(local_bytes), int(lent_bytes), flags,
                                  ctypes.byref(h)))
-    _HANDLES[h.value] = (bool(host_only), shape.dtype, int(num_kv_heads))
+    bb = 2 * shape.block_size * shape.num_kv_heads * shape.head_dim * 2
+    _HANDLES[h.value] = (bool(host_only), shape.dtype, int(num_kv_heads),
+                         int(local_bytes) // bb + int(lent_bytes) // bb)
     return h.value
 
 
@@ -257,8 +283,12 @@ def slice_lend(h, n_blocks):
 
 def _copy_call(fn, h, src, dst, n, stream):
     n = len(src) if n is None else int(n)
-    src, dst = _ids(h, src, n, "source ids"), _ids(h, dst, n, "destination ids")
-    _check(fn(h, _ptr(src), _ptr(dst), n, None if _host_only(h) else _stream(stream)))
+    if _host_only(h):
+        src, dst = _host_ids(src, n, "source ids"), _host_ids(dst, n, "destination ids")
+        _check(fn(h, _ptr(src), _ptr(dst), n, None))
+        return
+    _check(fn(h, _i32_dev(src, "source ids", n), _i32_dev(dst, "destination ids", n), n,
+              _stream(stream)))
 
 
 def slice_prefetch(h, block_ids, dst_block_table, n=None, stream=None):
@@ -274,7 +304,7 @@ def slice_migrate(h, src_ids, dst_ids, n=None, stream=None):
 def slice_prefetch_runs(h, src_first, dst_first, run_blocks, engine=0, stream=None):
     """Contiguous runs (host int arrays); engine ENGINE_KERNEL or ENGINE_DMA."""
     src_first, dst_first, run_blocks = (_i32_host(a) for a in (src_first, dst_first, run_blocks))
-    info_host = slice_get_info(h)["device"] < 0
+    info_host = _host_only(h)
     _check(_lib.ema_slice_prefetch_runs(h, src_first.ctypes.data, dst_first.ctypes.data,
                                         run_blocks.ctypes.data, len(run_blocks), int(engine),
                                         None if info_host else _stream(stream)))
@@ -290,35 +320,40 @@ def kv_append(h, k_new, v_new, block_table, seq_lens, stream=None):
     """k_new, v_new [B][Hkv][D] (16-bit), block_table int32 [B][max_blocks],
     seq_lens int32 [B] counting the new token: device tensors (numpy arrays
     for a host-only slice)."""
-    B = int(block_table.shape[0])
-    max_blocks = int(block_table.shape[1]) if block_table.ndim == 2 else 0
-    host = _host_only(h)
-    if host:
+    shape = block_table.shape
+    B = int(shape[0])
+    max_blocks = int(shape[1]) if len(shape) == 2 else 0
+    if _host_only(h):
         block_table, seq_lens = _i32_host(block_table), _i32_host(seq_lens)
-    else:
-        rec = _HANDLES.get(h)
-        row = rec[2] * 128 if rec else 0          # K/V elements per sequence
-        block_table = _i32_dev(block_table, "block_table", B * max_blocks)
-        seq_lens = _i32_dev(seq_lens, "seq_lens", B)
-        k_new = _kv16_dev(h, k_new, "k_new", B * row)
-        v_new = _kv16_dev(h, v_new, "v_new", B * row)
-    _check(_lib.ema_kv_append(h, _ptr(k_new), _ptr(v_new), _ptr(block_table), _ptr(seq_lens), B,
-                              max_blocks, None if host else _stream(stream)))
+        _check(_lib.ema_kv_append(h, _ptr(k_new), _ptr(v_new), _ptr(block_table), _ptr(seq_lens),
+                                  B, max_blocks, None))
+        return
+    rec = _HANDLES.get(h)
+    row = rec[2] * 128 if rec else 0          # K/V elements per sequence
+    kv16 = _kv16_types(rec)
+    table = _i32_dev(block_table, "block_table", B * max_blocks)
+    lens = _i32_dev(seq_lens, "seq_lens", B)
+    _check(_lib.ema_kv_append(h, _dev(k_new, "k_new", kv16, B * row),
+                              _dev(v_new, "v_new", kv16, B * row), table, lens, B, max_blocks,
+                              _stream(stream)))
 
 
 def slice_reclaim(h, n_blocks, canon_tables=None, stream=None, caps=None):
     """canon_tables: int32 device tensor rewritten in place (None for none).
     Returns the result counts, the victims (list) and the copies made
     ("moves": int64 array [moved][2] of (source, destination) unified ids)."""
-    info = slice_get_info(h)
-    cap = int(caps) if caps is not None else info["n_local"] + info["n_slice"]
+    rec = _HANDLES.get(h)
+    if rec is None:
+        info = slice_get_info(h)
+        rec = (info["device"] < 0, None, 0, info["n_local"] + info["n_slice"])
+    cap = int(caps) if caps is not None else rec[3]
     res = ReclaimResult()
     victims = np.empty(max(cap, 1), dtype=np.int32)
     msrc = np.empty(max(cap, 1), dtype=np.int32)
     mdst = np.empty(max(cap, 1), dtype=np.int32)
-    host_only = info["device"] < 0
+    host_only = rec[0]
     if canon_tables is not None and not host_only:
-        canon_tables = _i32_dev(canon_tables, "canon_tables")
+        _i32_dev(canon_tables, "canon_tables")
     n_entries = 0 if canon_tables is None else canon_tables.numel()
     _check(_lib.ema_slice_reclaim(h, int(n_blocks), _ptr(canon_tables), n_entries,
                                   None if host_only else _stream(stream), ctypes.byref(res),
@@ -331,19 +366,22 @@ def slice_reclaim(h, n_blocks, canon_tables=None, stream=None, caps=None):
 
 
 def _attention_call(fn, h, q, block_table, seq_lens, out, scale, stream):
-    import torch
-    B, Hq = int(q.shape[0]), int(q.shape[1])
-    max_blocks = int(block_table.shape[1]) if block_table.dim() == 2 else 0
-    out_types = {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}
-    if out.dtype not in out_types:
-        _bad(f"out: dtype {out.dtype} not in {tuple(out_types)}")
-    if not _host_only(h):
-        q = _kv16_dev(h, q, "q", B * Hq * 128)
-        block_table = _i32_dev(block_table, "block_table", B * max_blocks)
-        seq_lens = _i32_dev(seq_lens, "seq_lens", B)
-        out = _dev(out, "out", tuple(out_types), B * Hq * 128)
-    _check(fn(h, _ptr(q), _ptr(block_table), _ptr(seq_lens), B, Hq, max_blocks, float(scale),
-              _ptr(out), out_types[out.dtype], _stream(stream)))
+    T = _torch()
+    shape, tshape = q.shape, block_table.shape
+    B, Hq = int(shape[0]), int(shape[1])
+    max_blocks = int(tshape[1]) if len(tshape) == 2 else 0
+    code = T.out_codes.get(out.dtype)
+    if code is None:
+        _bad(f"out: dtype {out.dtype} not in {T.out_types}")
+    rec = _HANDLES.get(h)
+    if rec[0] if rec else _host_only(h):
+        args = _ptr(q), _ptr(block_table), _ptr(seq_lens), _ptr(out)
+    else:
+        args = (_dev(q, "q", _kv16_types(rec), B * Hq * 128),
+                _i32_dev(block_table, "block_table", B * max_blocks),
+                _i32_dev(seq_lens, "seq_lens", B), _dev(out, "out", T.out_types, B * Hq * 128))
+    _check(fn(h, args[0], args[1], args[2], B, Hq, max_blocks, float(scale), args[3], code,
+              _stream(stream)))
 
 
 def paged_decode_attention(h, q, block_table, seq_lens, out, scale=0.0, stream=None):
@@ -435,7 +473,7 @@ def slab_reclaim(h, n_slabs, canon_tables=None, stream=None):
     victims = np.empty(cap, dtype=np.int32)
     host_only = _host_only(h)
     if canon_tables is not None and not host_only:
-        canon_tables = _i32_dev(canon_tables, "canon_tables")
+        _i32_dev(canon_tables, "canon_tables")
     n_entries = 0 if canon_tables is None else canon_tables.numel()
     _check(_lib.ema_slab_reclaim(h, int(n_slabs), _ptr(canon_tables), n_entries,
                                  None if host_only else _stream(stream), ctypes.byref(res),
