@@ -48,7 +48,8 @@
 //
 // Masked tokens (past the length, or in a block whose id is out of range) get
 // -inf scores and zeroed V, so NaN in unused slots never leaks. Reduction
-// orders depend only on sequence lengths, not on block ids.
+// orders depend only on sequence lengths and the table's width, not on block
+// ids.
 #include "attn_store.h"
 #include "kernels.h"
 
@@ -70,6 +71,11 @@ constexpr int kWaves = 4;
 constexpr int kThreads = kWaves * 64;
 constexpr int kStreamWaves = 4;            // stream-K form
 constexpr int kStreamThreads = kStreamWaves * 64;
+constexpr int kDirectWaves = 8;            // direct form
+constexpr int kDirectThreads = kDirectWaves * 64;
+constexpr int kDirectPairs = 512;          // the most pairs it takes, and the longest, by the
+template <int BS>                          // width of the table (see attn_mfma_direct)
+constexpr int direct_tiles() { return BS >= 64 ? 8 : 16; }
 constexpr int kIt = 32;                    // tokens per tile (one wave iteration)
 constexpr int kPieceTiles = 32;            // tiles whose block ids are staged in LDS at once
 constexpr int kMaxIds = kPieceTiles * kIt / 16;
@@ -595,9 +601,9 @@ __device__ __forceinline__ void write_pair(const AttnArgs& a, int b, int kvh, co
 }
 
 // Merges channels [4 * d4, 4 * d4 + 4) of head g over parts first, second,
-// second + 2, ... (n <= K in all), read in one LDS round trip (indices past n
+// second + Step, ... (n <= K in all), read in one LDS round trip (indices past n
 // repeat the last part and are given weight 0).
-template <int G, int K>
+template <int G, int K, int Step>
 __device__ __forceinline__ void merge_parts(const Part<G>* p, int first, int second, int n, int g,
                                             int d4, float& M, float& L, f32x4& O) {
   float mm[K], ll[K];
@@ -605,7 +611,7 @@ __device__ __forceinline__ void merge_parts(const Part<G>* p, int first, int sec
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const int i = min(k, n - 1);
-    const Part<G>& q = p[i == 0 ? first : second + 2 * (i - 1)];
+    const Part<G>& q = p[i == 0 ? first : second + Step * (i - 1)];
     mm[k] = q.m[g];
     ll[k] = q.l[g];
     oo[k] = *reinterpret_cast<const f32x4*>(&q.o[g][4 * d4]);
@@ -814,7 +820,7 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
       const int g = e / (kD / 4), d4 = e % (kD / 4);
       float M, L;
       f32x4 O;
-      merge_parts<G, kStreamWaves>(parts, 0, 2, n, g, d4, M, L, O);
+      merge_parts<G, kStreamWaves, 2>(parts, 0, 2, n, g, d4, M, L, O);
       write_partial4<G>(a, 2 * blockIdx.x, g, d4, M, L, O);
     }
   }
@@ -827,7 +833,7 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
       const int g = e / (kD / 4), d4 = e % (kD / 4);
       float M, L;
       f32x4 O;
-      merge_parts<G, kStreamWaves>(parts, 2 * wave + 1, 2 * wave + 2, n, g, d4, M, L, O);
+      merge_parts<G, kStreamWaves, 2>(parts, 2 * wave + 1, 2 * wave + 2, n, g, d4, M, L, O);
       if (after)
         write_row4(a, row + g, d4, L, O);
       else
@@ -846,6 +852,63 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
   }
   for (int b = blockIdx.x; b < B; b += gridDim.x)
     if (s_len[b] == 0) write_zeros(a, b, kStreamThreads);
+}
+
+// Direct form, for few pairs that are short by the table's width: one
+// workgroup of eight wavefronts per (sequence, KV head), each streaming an
+// equal run of the pair's tiles, merged in LDS. No plan over all lengths and
+// no combine: one launch, and what it takes is the chain length - block id -
+// tile - merge. Against stream-K, 4 query heads to each of 8 KV heads, block
+// size 16, us a call: 8 pairs of up to 256 tokens 9.8 / 6.8, up to 512 9.7 / 7.5,
+// up to 1024 10.2 / 10.3; 256 pairs 12.9 / 7.6, 16.1 / 11.8, 21.4 / 19.3; 512
+// pairs 17.0 / 14.1, 22.4 / 21.0, 33.9 / 35.0; 1024 pairs 24.1 / 24.7, 34.9 /
+// 37.6. Block size 64: 32 pairs 9.9 / 7.3, 10.9 / 11.0; 512 pairs 18.1 / 14.3,
+// 24.4 / 25.3 -- hence up to 512 pairs, of 512 tokens, or 256 from block size 64
+// on (two tiles and one tile a wave).
+template <int G, int BS, bool BF16>
+__global__ __launch_bounds__(kDirectThreads, 2) void attn_mfma_direct(AttnArgs a) {
+  __shared__ Part<G> s_part[kDirectWaves];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = uniform(tid >> 6);
+  const int kvh = blockIdx.x;
+  const int b = blockIdx.y;
+  const int64_t row = int64_t(b) * a.q_heads + kvh * G;
+  const int raw = a.seq_lens[b];
+  const int len = clamp_len(raw, a);
+  if (kvh == 0 && tid == 0 && len != raw && raw > 0) atomicAdd(a.err_count, 1);
+  constexpr int kItems = G * (kD / 4);
+  if (len == 0) {
+    for (int e = tid; e < kItems; e += kDirectThreads)
+      store_out4(a, row * kD + 4 * e, out_f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+    return;
+  }
+  const int nt = (len + kIt - 1) / kIt;
+  const int per = (nt + kDirectWaves - 1) / kDirectWaves;
+  Group g;
+  g.b = b;
+  g.kvh = kvh;
+  g.len = len;
+  g.nt = nt;
+  g.j0 = min(nt, wave * per);
+  g.j1 = min(nt, g.j0 + per);
+  if (g.j0 < g.j1) {
+    first_group<BS>(g);
+    stream_wave<G, BS, BF16>(
+        a, g, [](Group& n) { return next_in_segment<BS>(n); },
+        [&](const Group&, float m, float lsum, const f32x4 (&o)[8]) {
+          put_part<G>(s_part[wave], m, lsum, o, lane & 15, lane >> 4);
+        });
+  }
+  __syncthreads();
+  const int n = (nt + per - 1) / per;
+  for (int e = tid; e < kItems; e += kDirectThreads) {
+    const int h = e / (kD / 4), d4 = e % (kD / 4);
+    float M, L;
+    f32x4 O;
+    merge_parts<G, kDirectWaves, 1>(s_part, 0, 1, n, h, d4, M, L, O);
+    write_row4(a, row + h, d4, L, O);
+  }
 }
 
 // Grid form for batches too large for the LDS work list: grid (chunk of
@@ -962,6 +1025,12 @@ __global__ __launch_bounds__(64) void attn_combine_streamk(AttnArgs a) {
 
 template <int G, int BS, bool BF16>
 hipError_t launch_typed(const AttnArgs& a, hipStream_t stream) {
+  if (a.stream_k && int64_t(a.max_blocks) * BS <= direct_tiles<BS>() * kIt &&
+      int64_t(a.batch) * a.kv_heads <= kDirectPairs) {
+    hipLaunchKernelGGL((attn_mfma_direct<G, BS, BF16>), dim3(a.kv_heads, a.batch),
+                       dim3(kDirectThreads), 0, stream, a);
+    return hipGetLastError();
+  }
   if (a.stream_k) {
     const int grid = attn_streamk_grid();
     hipLaunchKernelGGL((attn_mfma_streamk<G, BS, BF16>), dim3(grid), dim3(kStreamThreads), 0,

@@ -67,6 +67,52 @@ def test_ranges(ema, name):
         w.close()
 
 
+@pytest.mark.parametrize("hq,hkv,bs,dtype,batch,width", [
+    (8, 8, 16, "f16", 8, 32), (32, 8, 16, "bf16", 64, 32), (4, 1, 32, "bf16", 512, 16),
+    (16, 1, 64, "f16", 3, 4), (6, 3, 128, "bf16", 5, 2), (4, 2, 256, "bf16", 4, 1),
+    # one past each line of the rule: 513 pairs, 17 tiles, 9 tiles
+    (2, 1, 16, "bf16", 513, 32), (4, 2, 32, "f16", 4, 17), (8, 1, 64, "bf16", 4, 5)])
+def test_short_tables(ema, hq, hkv, bs, dtype, batch, width):
+    """Both sides of the line between the direct and the stream-K form: lengths
+    from 0 to the table's width, ids outside the pool, and the same outputs
+    from the entry point that allocates nothing."""
+    rng = np.random.default_rng(batch + bs)
+    lens = rng.integers(0, width * bs + 1, batch)
+    edge = [0, 1, 31, 32, 33, width * bs, max(1, width * bs - 1)]
+    lens[:min(len(edge), batch)] = edge[:batch]
+    lens[-1] = width * bs
+    cfg = synth.KVConfig("direct", 1, hq, hkv, 128, dtype, bs, batch, ("uniform", 0, 0), 0.0,
+                         4400 + batch)
+    w = Workload(cfg, lens=lens.tolist(), staging_slots=1)
+    try:
+        st = oracle_mirror(w)
+        assert w.attn_dev.shape[2] == width
+        out, na = w.new_out(), w.new_out()
+        out.fill_(float("nan"))
+        w.attention(0, out)
+        ema.paged_decode_attention_noalloc(w.h, w.q, w.attn_dev[0], w.lens_dev, na)
+        flat = torch.full((out.numel() + 1,), float("nan"), device="cuda")
+        odd = flat[1:].view(out.shape)
+        ema.paged_decode_attention(w.h, w.q, w.attn_dev[0], w.lens_dev, odd)
+        torch.cuda.synchronize()
+        assert ema.slice_device_errors(w.h) == 0
+        assert torch.equal(out, na) and torch.equal(out, odd)
+        got = out.cpu().numpy()
+        ref = oracle.paged_decode_attention(w.q16, w.attn_tables[0], w.lens, st.read_block, w.hkv,
+                                            w.D, w.bs, w.cfg.dtype)
+        assert rel_err(got, ref) <= TOL
+        assert (got[lens == 0] == 0).all()
+        # a sequence whose only block is no local block gives zeros and is counted
+        tab = w.attn_tables[0].copy()
+        tab[-1, :] = w.local_view.shape[0]
+        w.attention(0, out, table=torch.as_tensor(tab.astype(np.int32), device="cuda"))
+        torch.cuda.synchronize()
+        assert ema.slice_device_errors(w.h) >= 1
+        assert torch.equal(out[:-1], na[:-1]) and torch.count_nonzero(out[-1]) == 0
+    finally:
+        w.close()
+
+
 def test_several_id_lists_per_wave(ema):
     """80 sequences of about 4k tokens at 8 KV heads and block size 16: 80 tiles
     a wave, so its pieces go over several lists of 64 ids, 32 tiles each
