@@ -306,7 +306,8 @@ int ema_slice_reclaim(ema_slice_t h, int32_t n_blocks, int32_t* canon_tables, in
  * The result does not depend on which local blocks hold the tokens, bit for
  * bit. Async on `stream`.
  * Scheduling: stream-K over all (sequence, KV head) pairs when batch <= 4096
- * (2048 at 16 query heads per KV head), in the workspace allocated at create;
+ * (2048 at 16 query heads per KV head), in the workspace allocated at create
+ * (few pairs of short tables: one workgroup per pair, no workspace);
  * otherwise, or with EMA_CREATE_ATTN_GRID, a grid of 1024-token chunks whose
  * split-K workspace grows on first use (which synchronizes the device, frees
  * the smaller workspace -- graphs captured earlier with grid-form calls must
@@ -324,7 +325,7 @@ int ema_paged_decode_attention(ema_slice_t h, const void* q, const int32_t* bloc
  * paged_decode_attention_noalloc -- for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc): the same computation, arguments and result as
- * ema_paged_decode_attention, always in the stream-K form, with its partials
+ * ema_paged_decode_attention, never in the grid form, with its partials
  * and combine records in a fixed per-GPU workspace (a file-scope device array
  * of about 8.5 MB, held by each GPU the library runs on until the process
  * ends) instead of the handle's. The call allocates nothing, on the device or

@@ -87,7 +87,8 @@ struct AttnArgs {
   void* out;                // [B][Hq][128], out_dtype
   float* part_o;            // [B][Hq][n_split][128] split-K partial outputs
   float* part_ml;           // [B][Hq][n_split][2] running max (log2 domain) and sum
-                            // (stream-K: [2 * grid][G][...] partial slots instead)
+                            // (stream-K: [2 * grid][G][...] partial slots instead; not used
+                            // by the direct form)
   int32_t* info;            // stream-K: [grid][2] pair that begins in a workgroup and goes on
                             // past it (-1: none), last workgroup that holds it
   int32_t* err_count;
@@ -108,10 +109,9 @@ constexpr int kOutBF16 = 1;
 constexpr int kOutF32 = 2;
 
 constexpr int kMfmaGridChunk = 1024;   // tokens per workgroup of the matrix-core grid form
-// Sequences the stream-K work list holds in LDS (lengths and prefix sums):
-// sized so that a workgroup's LDS stays within half a CU's 160 KiB, which
-// every call measured faster (16 query heads per KV head need twice the
-// merge space, hence the smaller list).
+// Sequences whose lengths the stream-K form holds in LDS: with the partials of
+// four wavefronts (16 query heads per KV head need twice the space, hence the
+// smaller list) a workgroup's LDS stays within half a CU's 160 KiB.
 constexpr int streamk_max_batch(int group) { return group >= 16 ? 2048 : 4096; }
 constexpr int kMaxStreamGrid = 2048;   // stream-K workgroups (partial slots: 2 each)
 constexpr int kHeadDim = 128;          // the only head size the device paths take
@@ -135,8 +135,8 @@ constexpr size_t kNoAllocBytes = kNoAllocPartFloats * 4 + size_t(kNoAllocGrid) *
 // device with hipGetSymbolAddress, then cached).
 hipError_t noalloc_workspace(void** ptr);
 
-// Matrix-core kernel: stream-K when stream_k is set, else the grid form with
-// chunk == kMfmaGridChunk.
+// Matrix-core kernel: when stream_k is set the stream-K form, or the direct one
+// for few short pairs; else the grid form with chunk == kMfmaGridChunk.
 hipError_t launch_paged_attention_mfma(const AttnArgs& a, hipStream_t stream);
 // Merges the split-K partials of sequences longer than one chunk.
 hipError_t launch_attn_combine(const AttnArgs& a, hipStream_t stream);

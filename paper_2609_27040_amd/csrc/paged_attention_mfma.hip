@@ -95,21 +95,15 @@ __device__ __forceinline__ u32x4 ld16(const char* p) {
 __device__ __forceinline__ u32x4 ld16_stream(const char* p) {
   return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
 }
-// But a line that a wave reads in two halves, tiles or instructions apart, has
-// to stay in L2 in between, and a streamed one may not. From block size 64 on a
-// tile's V rows are 64-byte pieces of rows of 128 bytes and more, the rest of
-// which the next tile reads; a K row's lines are read 64 bytes at a time by
-// successive instructions. Measured, us a call with all streamed / V kept / K
-// and V kept: block size 64, 64 sequences of 1024-4096 tokens, 8 KV heads 158 /
-// 130 / 128; 256, the same 157 / 131 / 127; streamed / K kept / K and V kept:
-// block size 16, the same 114.1 / 113.3 / 125.3; block size 32, one KV head,
-// 128 sequences 44.1 / 44.6 / 48.5.
+// But a line that a wave reads in two halves, tiles apart, has to stay in L2 in
+// between, and a streamed one may not: from block size 64 on a tile's V rows
+// are 64-byte pieces of rows of 128 bytes and more, the rest of which the next
+// tile reads. Measured, us a call with K and V streamed / V kept / both kept: 64
+// sequences of 1024-4096 tokens, 8 KV heads, block size 64 158 / 130 / 128, 256
+// 157 / 131 / 127; streamed / K kept / both kept: block size 16 108.1 / 108.7 /
+// 119, block size 32, one KV head, 128 sequences 44.1 / 44.6 / 48.5.
 template <int BS>
-__device__ __forceinline__ u32x4 ld16_k(const char* p) {
-  return BS == 32 ? ld16_stream(p) : ld16(p);
-}
-template <int BS>
-__device__ __forceinline__ u32x4 ld16_v(const char* p) {
+__device__ __forceinline__ u32x4 ld16_kv(const char* p) {
   return BS >= 64 ? ld16(p) : ld16_stream(p);
 }
 
@@ -435,7 +429,7 @@ __device__ __forceinline__ void load_tile_ids(Tile& T, const AttnArgs& a, const 
     const char* base = (BS == 16 && in && tok >= 16) ? base1 : base0;
     const char* p = base + (khead + row * kD * 2 + q4 * 16);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) T.k[t][kk] = ld16_k<BS>(p + kk * 64);
+    for (int kk = 0; kk < 4; ++kk) T.k[t][kk] = ld16_kv<BS>(p + kk * 64);
   }
   // V^T rows: d-tile n, row 16n + r16, tokens t0 + 8q4 .. +8 (one block).
   const int vt = 8 * q4;
@@ -446,7 +440,7 @@ __device__ __forceinline__ void load_tile_ids(Tile& T, const AttnArgs& a, const 
   const int64_t vhead = Bb / 2 + (g.kvh * kD * BS + tb) * 2;
   const char* p = (second ? base1 : base0) + vhead + vrow * 2;
 #pragma unroll
-  for (int n = 0; n < 8; ++n) T.v[n] = ld16_v<BS>(p + 16 * n * BS * 2);
+  for (int n = 0; n < 8; ++n) T.v[n] = ld16_kv<BS>(p + 16 * n * BS * 2);
 }
 
 // Q^T of one pair as the B operand: lane (head r16, q4) holds channels
