@@ -551,7 +551,7 @@ hipError_t launch_copy(const PoolView& pv, CopyIds ids, int32_t n, int32_t* err_
       // whole workgroups of a block, up to 256 KiB, to an XCD; full rounds only
       const int64_t groups = int64_t(m) * upb / kWaves;
       const uint32_t run = uint32_t(std::min(upb, kXcdRunBytes / kPieceBytes) / kWaves);
-      const uint32_t limit = pv.block_bytes <= 65536
+      const uint32_t limit = pv.block_bytes <= 65536 || runs
                                  ? 0
                                  : uint32_t(groups / (8 * int64_t(run)) * (8 * int64_t(run)));
       hipLaunchKernelGGL(block_copy_same_kernel, dim3(unsigned(grid)), dim3(256), 0, stream,
