@@ -42,7 +42,8 @@
  *   split-K workspace: do not run two of them concurrently on different
  *   streams. Reclaim and run prefetches share the handle's plan upload area
  *   and order themselves on the device (a later call's stream waits for the
- *   earlier call's kernels), so they may be issued on different streams.
+ *   earlier call's kernels), so they may be issued on different streams; so
+ *   may slab swaps, which share the handle's source lists.
  *   Device paths support head_dim 128 and block_size in {16,32,64,128,256}.
  *   Device id arrays are validated on the host only when the slice was
  *   created with EMA_CREATE_CHECKED (it costs a device-to-host copy). Without

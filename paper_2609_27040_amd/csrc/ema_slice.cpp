@@ -24,6 +24,9 @@
 #include "kernels.h"
 #include "slice_book.h"
 
+// Readers of the slab lists that may be under way without waiting for each other.
+constexpr uint32_t kSlabUses = 8;
+
 struct ema_slice {
   ema_kv_shape shape{};
   int64_t bb = 0;
@@ -55,10 +58,11 @@ struct ema_slice {
   int32_t* h_slab = nullptr;        // pinned
   size_t slab_cap = 0;              // ints
   int64_t slab_built = -1;          // slab version the device lists were built for
-  int32_t slab_m = 0;               // borrowed slabs when they were built
   hipEvent_t slab_up_ev = nullptr;  // after the last upload of the lists
-  hipEvent_t slab_use_ev = nullptr; // after the last kernel that read them
-  bool slab_up_pending = false, slab_use_pending = false;
+  bool slab_up_pending = false;     // not yet waited for on the host
+  bool slab_up_recorded = false;    // the event stands for the lists' upload
+  hipEvent_t slab_use_ev[kSlabUses] = {};   // after the last kernels that read them
+  uint32_t slab_uses = 0;           // how many have been launched
 };
 
 namespace {
@@ -157,11 +161,18 @@ int fetch_ints(const int32_t* dev, int64_t n, hipStream_t st, std::vector<int32_
   return EMA_OK;
 }
 
-int grow_device(void** p, size_t* cap, size_t need, size_t elem, hipStream_t st) {
-  if (need <= *cap) return EMA_OK;
+int is_capturing(hipStream_t st, bool* yes) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   HIP_TRY(hipStreamIsCapturing(st, &cs), "hipStreamIsCapturing");
-  if (cs != hipStreamCaptureStatusNone)
+  *yes = cs != hipStreamCaptureStatusNone;
+  return EMA_OK;
+}
+
+int grow_device(void** p, size_t* cap, size_t need, size_t elem, hipStream_t st) {
+  if (need <= *cap) return EMA_OK;
+  bool capturing;
+  if (int rc = is_capturing(st, &capturing)) return rc;
+  if (capturing)
     return fail(EMA_ERR_INVAL, "attention: the grid-form workspace would grow during stream "
                                "capture; run a call of this size once before capturing");
   HIP_TRY(hipDeviceSynchronize(), "hipDeviceSynchronize(grow)");
@@ -198,7 +209,8 @@ void release(ema_slice* h) {
     if (h->d_slab) (void)hipFree(h->d_slab);
     if (h->h_slab) (void)hipHostFree(h->h_slab);
     if (h->slab_up_ev) (void)hipEventDestroy(h->slab_up_ev);
-    if (h->slab_use_ev) (void)hipEventDestroy(h->slab_use_ev);
+    for (hipEvent_t ev : h->slab_use_ev)
+      if (ev) (void)hipEventDestroy(ev);
   }
   delete h;
 }
@@ -272,6 +284,52 @@ int upload(ema_slice* h, size_t n_ints, hipStream_t st) {
 int end_upload(ema_slice* h, hipStream_t st) {
   HIP_TRY(hipEventRecord(h->d_work_ev, st), "hipEventRecord(kernels)");
   h->d_work_pending = true;
+  return EMA_OK;
+}
+
+// The slab lists in d_slab are uploaded by the first swap after the set of
+// borrowed slabs changed and read by every later one, on whatever streams the
+// caller issues them: an upload waits for the kernels that read the previous
+// lists, a reader for the upload. Readers do not wait for each other; the event
+// of each is kept until kSlabUses later ones have been launched, and the one
+// that takes its place waits for it first, so the events kept always cover every
+// reader. (Waiting for the own stream's work, or for work already done, costs
+// nothing.) A capturing stream can neither wait for work outside its graph nor
+// leave an event for such work: there the caller orders the replays, as for
+// every graph.
+int slab_upload(ema_slice* h, int32_t m, hipStream_t st, bool capturing) {
+  const ema::SlabCfg& c = h->book.slab_cfg();
+  if (size_t(m) * c.layers * c.slab_blocks > h->slab_cap)
+    return fail(EMA_ERR_INVAL, "slab_prefetch_group: lists larger than their buffer");
+  if (h->slab_up_pending) {
+    HIP_TRY(hipEventSynchronize(h->slab_up_ev), "hipEventSynchronize(slab lists)");
+    h->slab_up_pending = false;
+  }
+  for (uint32_t i = 0; i < std::min(h->slab_uses, kSlabUses); ++i)
+    HIP_TRY(hipStreamWaitEvent(st, h->slab_use_ev[i], 0), "hipStreamWaitEvent(slab lists)");
+  std::vector<int32_t> src;
+  size_t off = 0;
+  for (int32_t g = 0; g < c.layers / c.group; ++g) {
+    h->book.group_sources(g, &src);
+    std::copy(src.begin(), src.end(), h->h_slab + off);
+    off += src.size();
+  }
+  HIP_TRY(hipMemcpyAsync(h->d_slab, h->h_slab, off * 4, hipMemcpyHostToDevice, st),
+          "hipMemcpyAsync(slab lists)");
+  if (!capturing) HIP_TRY(hipEventRecord(h->slab_up_ev, st), "hipEventRecord(slab lists)");
+  h->slab_up_pending = h->slab_up_recorded = !capturing;
+  h->slab_built = h->book.slab_version();
+  return EMA_OK;
+}
+
+// After a launch on `st` that reads the slab lists.
+int slab_used(ema_slice* h, hipStream_t st) {
+  hipEvent_t ev = h->slab_use_ev[h->slab_uses % kSlabUses];
+  if (h->slab_uses >= kSlabUses)
+    HIP_TRY(hipStreamWaitEvent(st, ev, 0), "hipStreamWaitEvent(slab swap)");
+  HIP_TRY(hipEventRecord(ev, st), "hipEventRecord(slab swap)");
+  // from kSlabUses on the count only tells the event whose turn it is
+  h->slab_uses = h->slab_uses + 1 < 2 * kSlabUses ? h->slab_uses + 1 : kSlabUses;
   return EMA_OK;
 }
 
@@ -843,7 +901,8 @@ int ema_slab_init(ema_slice_t h, const ema_slab_cfg* cfg) try {
     e = hipMalloc(&h->d_slab, cap * 4);
     if (e == hipSuccess) e = hipHostMalloc(&h->h_slab, cap * 4, hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->slab_up_ev, hipEventDisableTiming);
-    if (e == hipSuccess) e = create_use_event(&h->slab_use_ev);
+    for (uint32_t i = 0; i < kSlabUses && e == hipSuccess; ++i)
+      e = create_use_event(&h->slab_use_ev[i]);
     if (e != hipSuccess) return hip_fail(e, "slab_init");
     h->slab_cap = cap;
   }
@@ -1017,34 +1076,16 @@ int ema_slab_prefetch_group(ema_slice_t h, int32_t group, int32_t staging_first,
       return EMA_OK;
     }
   }
-  if (h->slab_built != h->book.slab_version()) {
-    // every group's sources, rebuilt only when the set of borrowed slabs changed
-    if (size_t(m) * c.layers * c.slab_blocks > h->slab_cap)
-      return fail(EMA_ERR_INVAL, "slab_prefetch_group: lists larger than their buffer");
-    if (h->slab_up_pending) {
-      HIP_TRY(hipEventSynchronize(h->slab_up_ev), "hipEventSynchronize(slab lists)");
-      h->slab_up_pending = false;
-    }
-    if (h->slab_use_pending) HIP_TRY(hipStreamWaitEvent(st, h->slab_use_ev, 0), "hipStreamWaitEvent");
-    std::vector<int32_t> src;
-    size_t off = 0;
-    for (int32_t g = 0; g < c.layers / c.group; ++g) {
-      h->book.group_sources(g, &src);
-      std::copy(src.begin(), src.end(), h->h_slab + off);
-      off += src.size();
-    }
-    HIP_TRY(hipMemcpyAsync(h->d_slab, h->h_slab, off * 4, hipMemcpyHostToDevice, st),
-            "hipMemcpyAsync(slab lists)");
-    HIP_TRY(hipEventRecord(h->slab_up_ev, st), "hipEventRecord(slab lists)");
-    h->slab_up_pending = true;
-    h->slab_built = h->book.slab_version();
-    h->slab_m = m;
-  }
+  bool capturing;
+  if ((rc = is_capturing(st, &capturing))) return rc;
+  // every group's sources, rebuilt only when the set of borrowed slabs changed
+  if (h->slab_built != h->book.slab_version() && (rc = slab_upload(h, m, st, capturing))) return rc;
+  if (!capturing && h->slab_up_recorded)
+    HIP_TRY(hipStreamWaitEvent(st, h->slab_up_ev, 0), "hipStreamWaitEvent(slab upload)");
   HIP_TRY(ema::launch_block_copy(pool_view(h), h->d_slab + size_t(group) * count, nullptr,
                                  int32_t(count), h->d_err, st, true, nullptr, staging_first),
           "slab_prefetch_group launch");
-  HIP_TRY(hipEventRecord(h->slab_use_ev, st), "hipEventRecord(slab prefetch)");
-  h->slab_use_pending = true;
+  if (!capturing && (rc = slab_used(h, st))) return rc;
   return EMA_OK;
 } catch (...) {
   return internal_error();

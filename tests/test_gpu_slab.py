@@ -198,6 +198,56 @@ def test_swap_lists_follow_the_borrowed_set(ema):
         c.close()
 
 
+@pytest.mark.parametrize("readers", [2, 12])
+def test_swaps_on_two_streams_share_the_source_lists(ema, readers):
+    """Swaps on two streams with no host synchronisation between them. The first
+    call's stream is held up by a long copy, so when the second stream's swap is
+    issued the lists it reads are not uploaded yet; then the borrowed set
+    changes, and the second stream's next swap rebuilds the lists while the
+    first stream's swaps have still to read the old ones (two swaps, and more
+    of them than the handle keeps events for). Both pools must equal the
+    oracle's, which runs the calls one after the other."""
+    print(f"slab lists on two streams, {readers} readers", flush=True)
+    c = SlabCache(ema, oracle.LAYER_MAJOR, 0, n_slabs=120, S=1, B=24, seed=21)
+    st = c.st
+    try:
+        # every other slab of 40 more freed: more runs than a launch's
+        # arguments hold, and a change that leaves other sources behind
+        p = ema.slab_alloc(c.h, np.arange(40) % 7)
+        assert np.array_equal(p, st.slab_alloc(np.arange(40) % 7))
+        ema.slab_free(c.h, p[::2])
+        st.slab_free(p[::2])
+        m = len(st.borrowed())
+        ids = ema.slice_alloc_blocks(c.h, ema.POOL_LOCAL, [ema.STAGING] * (3 * c.k * (m + 20)))
+        st.alloc_blocks(oracle.LOCAL, [oracle.STAGING] * (3 * c.k * (m + 20)))
+        assert np.array_equal(ids, ids[0] + np.arange(len(ids)))
+        img = [int(ids[0]) + i * c.k * (m + 20) for i in range(3)]
+        assert all(len(ema.slab_group_runs(c.h, g, img[0])[0]) > 24 for g in range(c.L // c.k))
+        big = torch.empty(8 << 30, dtype=torch.uint8, device="cuda")
+        big2 = torch.empty_like(big)
+        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s1):
+            big2.copy_(big)                            # keeps s1 busy for milliseconds
+        for i in range(readers - 1):
+            ema.slab_prefetch_group(c.h, 0, img[0], stream=s1)   # the first uploads the lists
+        ema.slab_prefetch_group(c.h, 1, img[1], stream=s2)
+        st.prefetch_group(0, img[0])
+        st.prefetch_group(1, img[1])
+        # other slabs: the freed ones borrowed again
+        q = ema.slab_alloc(c.h, [9] * 20)
+        assert np.array_equal(q, st.slab_alloc([9] * 20))
+        ema.slab_prefetch_group(c.h, 0, img[2], stream=s2)       # rebuilds the lists
+        st.prefetch_group(0, img[2])
+        torch.cuda.synchronize()
+        del big, big2
+        assert np.array_equal(c.lv.cpu().numpy(), st.local)
+        assert np.array_equal(c.sv.cpu().numpy(), st.slice)
+        assert ema.slice_device_errors(c.h) == 0
+    finally:
+        c.close()
+
+
 @pytest.mark.parametrize("mode", ["serial", "overlap"])
 @pytest.mark.parametrize("engine", [0, 1])
 @pytest.mark.parametrize("S,k", [(1, 1), (3, 2), (10, 4)])
