@@ -89,8 +89,9 @@ struct AttnArgs {
   float* part_ml;           // [B][Hq][n_split][2] running max (log2 domain) and sum
                             // (stream-K: [2 * grid][G][...] partial slots instead; not used
                             // by the direct form)
-  int32_t* info;            // stream-K: [grid][2] pair that begins in a workgroup and goes on
-                            // past it (-1: none), last workgroup that holds it
+  int32_t* info;            // stream-K: [grid][2] combine records: pair that begins in a
+                            // workgroup and goes on past it (-1: none), last workgroup that
+                            // holds it; or, of at most grid pairs, first (-1) and last workgroup
   int32_t* err_count;
   const char* local;        // local pool base
   int64_t block_bytes;

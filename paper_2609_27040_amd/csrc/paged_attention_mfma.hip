@@ -73,6 +73,7 @@ constexpr int kStreamWaves = 4;            // stream-K form
 constexpr int kStreamThreads = kStreamWaves * 64;
 constexpr int kDirectWaves = 8;            // direct form
 constexpr int kDirectThreads = kDirectWaves * 64;
+constexpr int kCombineWaves = 4;           // stream-K form's combine
 constexpr int kDirectPairs = 512;          // the most pairs it takes, and the longest, by the
 template <int BS>                          // width of the table (see attn_mfma_direct)
 constexpr int direct_tiles() { return BS >= 64 ? 8 : 16; }
@@ -657,6 +658,16 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
   return x;
 }
 
+// Combine records of the stream-K form: one per workgroup (the pair that begins
+// there and goes on past it, its last workgroup), or one per pair (its first and
+// last workgroup) where there are no more pairs than workgroups, so that few
+// pairs take a combine of few workgroups (3 sequences of 100-900 tokens at 8
+// heads to each of 8 KV heads: 12.2 -> 11.4 us a call). First value -1: nothing
+// to combine.
+__host__ __device__ __forceinline__ bool records_by_pair(const AttnArgs& a, int64_t grid) {
+  return int64_t(a.batch) * a.kv_heads <= grid;
+}
+
 // Stream-K form. The units of all (sequence, KV head) pairs, in that order --
 // each pair's kSegCost cost units (no tiles), then its tiles -- are cut into
 // equal contiguous ranges, one per wavefront. A pair that lies within one
@@ -666,8 +677,8 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
 // waves merge these: a pair that began and ended within the workgroup is
 // written, one that crosses a workgroup boundary leaves one partial in global
 // memory -- slot 2w for the pair workgroup w entered in its middle, 2w + 1 for
-// the one that begins there and goes on -- and a record (pair, last
-// workgroup), by the workgroup it begins in, for the combine.
+// the one that begins there and goes on -- and a record, written by the
+// workgroup it begins in, for the combine.
 template <int G, int BS, bool BF16>
 // Compiled as if two workgroups shared a CU (at most 256 registers a lane),
 // although one per CU is launched: under the looser bound the compiler's
@@ -687,6 +698,7 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
   const int q4 = lane >> 4;
   const int B = a.batch;
   const int H = a.kv_heads;
+  const bool by_pair = records_by_pair(a, gridDim.x);
 
   // Every workgroup reads all lengths: thread t takes per_t consecutive
   // sequences, loaded four at a time (one round trip up to 1024 sequences).
@@ -786,6 +798,7 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
         put_part<G>(p, m, lsum, o, r16, q4);
         if (begins && ends) {
           write_pair<G>(a, c.b, c.kvh, p, lane);
+          if (by_pair && lane == 0) a.info[2 * (c.b * H + c.kvh)] = -1;
           return;
         }
         if (begins) {
@@ -833,8 +846,12 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
       else
         write_partial4<G>(a, 2 * blockIdx.x + 1, g, d4, M, L, O);
     }
+    if (by_pair && lane == 0) {
+      a.info[2 * tail] = after ? -1 : int(blockIdx.x);
+      a.info[2 * tail + 1] = tail_wg;
+    }
   }
-  if (tid < 64) {
+  if (!by_pair && tid < 64) {
     // the last tail of the workgroup goes on past it if no later head ends
     const uint64_t tails = __ballot(lane < kStreamWaves && mine.z >= 0);
     const int w = tails ? 63 - __builtin_clzll(tails) : 0;
@@ -845,7 +862,11 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
     }
   }
   for (int b = blockIdx.x; b < B; b += gridDim.x)
-    if (s_len[b] == 0) write_zeros(a, b, kStreamThreads);
+    if (s_len[b] == 0) {
+      write_zeros(a, b, kStreamThreads);
+      if (by_pair)
+        for (int h = tid; h < H; h += kStreamThreads) a.info[2 * (b * H + h)] = -1;
+    }
 }
 
 // Direct form, for few pairs that are short by the table's width: one
@@ -984,34 +1005,69 @@ struct Partials {
 };
 
 // Merges the partials of every pair that crosses a stream-K workgroup
-// boundary: grid (stream-K workgroup the pair begins in, heads by two), one
-// wavefront each, one lane per four channels of a head. The record, then up
-// to 4 partials in one round trip, or 16 at a time where a pair has more (one
-// sequence of 30000 tokens over 32 workgroups per head: 30.3 us a call, with
-// 4 at a time 34.5). Loading the first partials along with the record costs
-// more than it saves: most workgroups have no pair to merge, and the call with
-// 16 pairs of 8 heads took 21.2 us instead of 19.6.
+// boundary: grid (record, heads by two), one lane per four channels of a head.
+// The record, then one wavefront merges up to 4 partials, read in one round
+// trip; more are shared out over the workgroup's kCombineWaves wavefronts
+// (consecutive ones to each, up to 16 a round trip), whose results one of them
+// merges. What bounds it is that chain of round trips, about 2 us each. One
+// wavefront for all partials / four / eight, us a call: one sequence of 30000
+// tokens over 235 workgroups, 16 heads 43.7 / 19.6 / 17.0, two of 20-60
+// thousand, 8 heads 32.3 / 21.1 / 20.6; 512 sequences of 17-1000 tokens, 16
+// heads 38.0 / 38.4 / 39.8. Of these the record by pair is 30.2 -> 19.6 and
+// 27.7 -> 21.1. Loading the first partials along with the record costs more
+// than it saves: most workgroups have no pair to merge, and a call with 16
+// pairs of 8 heads took 21.2 us instead of 19.6.
 template <int G>
-__global__ __launch_bounds__(64) void attn_combine_streamk(AttnArgs a) {
-  const int w0 = blockIdx.x;
-  const int pair = a.info[2 * w0], last_wg = a.info[2 * w0 + 1];
-  const int e = blockIdx.y * 64 + threadIdx.x;
-  if (pair < 0 || e >= G * (kD / 4)) return;
-  const int g = e / (kD / 4), d4 = e % (kD / 4);
+__global__ __launch_bounds__(kCombineWaves * 64) void attn_combine_streamk(AttnArgs a, bool by_pair) {
+  __shared__ __attribute__((aligned(16))) f32x4 s_o[kCombineWaves][64];
+  __shared__ float s_ml[kCombineWaves][64][2];
+  const int rec = a.info[2 * blockIdx.x], last_wg = a.info[2 * blockIdx.x + 1];
+  const int w0 = by_pair ? rec : int(blockIdx.x);
+  const int pair = by_pair ? int(blockIdx.x) : rec;
+  const int wave = uniform(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
   const int n = last_wg - w0 + 1;
+  if (rec < 0 || (wave > 0 && n <= 4)) return;
+  // G = 1: the upper half of the lanes repeats the lower half's work
+  const int e = (blockIdx.y * 64 + lane) % (G * (kD / 4));
+  const int g = e / (kD / 4), d4 = e % (kD / 4);
   float M = -INFINITY, L = 0.0f;
   f32x4 O = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (n <= 4) {
+  const int per = n <= 4 ? n : (n + kCombineWaves - 1) / kCombineWaves;
+  const int i1 = min(n, (wave + 1) * per);
+  if (per <= 4) {
     Partials<G, 4> p;
-    p.load(a, w0, 0, last_wg, g, d4);
-    p.merge(n, M, L, O);
+    p.load(a, w0, min(wave * per, n - 1), last_wg, g, d4);
+    p.merge(i1 - wave * per, M, L, O);
   } else {
-    for (int i0 = 0; i0 < n; i0 += 16) {
+    for (int i0 = wave * per; i0 < i1; i0 += 16) {
       Partials<G, 16> p;
       p.load(a, w0, i0, last_wg, g, d4);
-      p.merge(n - i0, M, L, O);
+      p.merge(i1 - i0, M, L, O);
     }
   }
+  if (n > 4) {
+    s_ml[wave][lane][0] = M;
+    s_ml[wave][lane][1] = L;
+    s_o[wave][lane] = O;
+    __syncthreads();
+    if (wave > 0) return;
+    float Mw = M;
+#pragma unroll
+    for (int w = 1; w < kCombineWaves; ++w) Mw = fmaxf(Mw, s_ml[w][lane][0]);
+    L = 0.0f;
+    O = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int w = 0; w < kCombineWaves; ++w) {
+      const float m = s_ml[w][lane][0];
+      if (m == -INFINITY) continue;
+      const float f = exp2f(m - Mw);
+      L = fmaf(f, s_ml[w][lane][1], L);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) O[c] = fmaf(f, s_o[w][lane][c], O[c]);
+    }
+  }
+  if (G == 1 && lane >= 32) return;
   const int H = a.kv_heads;
   const int b = pair / H;
   write_row4(a, int64_t(b) * a.q_heads + (pair - b * H) * G + g, d4, L, O);
@@ -1031,7 +1087,10 @@ hipError_t launch_typed(const AttnArgs& a, hipStream_t stream) {
                        stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_combine_streamk<G>, dim3(grid, (G + 1) / 2), dim3(64), 0, stream, a);
+    const bool by_pair = records_by_pair(a, grid);
+    hipLaunchKernelGGL(attn_combine_streamk<G>,
+                       dim3(by_pair ? a.batch * a.kv_heads : grid, (G + 1) / 2),
+                       dim3(kCombineWaves * 64), 0, stream, a, by_pair);
     return hipGetLastError();
   }
   hipLaunchKernelGGL((attn_mfma_grid<G, BS, BF16>), dim3(a.n_split, a.kv_heads, a.batch),

@@ -28,9 +28,9 @@ def ema():
 
 
 CASES = {
-    # one pair over every workgroup: 20k tokens, 625 tiles over 1024 waves
-    "one-long": (4, 1, 16, "bf16", [0, 20001, 0]),
-    # 4 heads of one long sequence: each crosses about 64 workgroups
+    # one pair over every workgroup of 256: 1022 tiles over 1024 waves
+    "one-long": (4, 1, 16, "bf16", [0, 32690, 0]),
+    # 4 heads of one long sequence: each crosses 36 workgroups of 256
     "long-16-heads": (64, 4, 32, "f16", [0, 0, 9000, 33]),
     # one tile a pair, eight pairs a wave and more
     "short": (16, 8, 16, "f16", [1 + i % 32 for i in range(1500)]),
@@ -63,6 +63,35 @@ def test_ranges(ema, name):
         ref = oracle.paged_decode_attention(w.q16, w.attn_tables[0], w.lens, st.read_block, w.hkv,
                                             w.D, w.bs, w.cfg.dtype)
         assert rel_err(out.cpu().numpy(), ref) <= TOL
+    finally:
+        w.close()
+
+
+@pytest.mark.parametrize("tiles", [14, 17, 18, 62, 63, 254, 255, 1022, 1023, 2500])
+@pytest.mark.parametrize("hq,others", [(1, 0), (16, 0), (8, 3), (4, 300)])
+def test_partials_of_one_pair(ema, hq, others, tiles):
+    """A pair cut over n workgroups, n at the edges of the combine's rounds (4,
+    5, 16, 17, 64, 65 and 256 of 256 workgroups): alone, with a few more pairs
+    (a record per pair) and after more pairs than workgroups (a record per
+    workgroup)."""
+    print(f"partials hq={hq} others={others} tiles={tiles}", flush=True)
+    lens = [1 + i % 40 for i in range(others)] + [32 * tiles - 5]
+    cfg = synth.KVConfig("partials", 1, hq, 1, 128, "f16", 64, len(lens), ("uniform", 0, 0), 0.0,
+                         4500 + tiles)
+    w = Workload(cfg, lens=lens, staging_slots=1)
+    try:
+        st = oracle_mirror(w)
+        table = torch.full((len(lens), w.attn_dev.shape[2] + 16), -1, dtype=torch.int32, device="cuda")
+        table[:, :w.attn_dev.shape[2]] = w.attn_dev[0]
+        out = w.new_out()
+        for _ in range(2):
+            out.fill_(float("nan"))
+            w.attention(0, out, table=table)
+            torch.cuda.synchronize()
+            assert ema.slice_device_errors(w.h) == 0
+            ref = oracle.paged_decode_attention(w.q16, w.attn_tables[0], w.lens, st.read_block,
+                                                w.hkv, w.D, w.bs, w.cfg.dtype)
+            assert rel_err(out.cpu().numpy(), ref) <= TOL
     finally:
         w.close()
 
