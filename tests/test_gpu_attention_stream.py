@@ -142,6 +142,59 @@ def test_short_tables(ema, hq, hkv, bs, dtype, batch, width):
         w.close()
 
 
+@pytest.mark.parametrize("hq,hkv,bs,dtype,batch,lo,hi,bound", [
+    (32, 8, 16, "bf16", 64, 1024, 4096, 2.9e-6), (32, 8, 16, "bf16", 64, 17, 1000, 2.9e-6),
+    (8, 1, 32, "bf16", 64, 128, 6000, 2.9e-6), (16, 1, 64, "bf16", 32, 100, 9000, 2.9e-6),
+    (8, 8, 16, "bf16", 8, 64, 512, 2.9e-6),
+    (32, 8, 16, "f16", 64, 1024, 4096, 3.1e-7), (32, 8, 16, "f16", 64, 17, 1000, 2.0e-7),
+    (8, 8, 64, "f16", 64, 200, 1500, 2.4e-7), (64, 8, 16, "f16", 256, 17, 300, 1.9e-7),
+    (32, 2, 32, "f16", 4, 30000, 90000, 3.4e-7), (8, 8, 16, "f16", 8, 64, 512, 2.0e-7)])
+def test_error_against_64_bits(ema, hq, hkv, bs, dtype, batch, lo, hi, bound):
+    """2-norm of the error over 2-norm of the result, normal values, fp32 output.
+
+    bf16: probabilities are two parts rounded to nearest, which leaves a
+    remainder of 2^-8 rounded to 8 bits: 2.5e-6 of a probability (root mean
+    square over its binade), so 2.5e-6 of a sum over independent values, plus
+    the fp32 sums' few 1e-7: 2.9e-6. A truncated high part gives twice that (3.5
+    to 4.4e-6 measured).
+    f16 keeps 22 bits, so the scores' and the sums' fp32 roundings show. The
+    bounds are what four waves to a pair, each with every fourth tile, measured
+    (3.09e-7, 1.94e-7, 2.33e-7, 1.80e-7, 3.42e-7 and 1.90e-7 in this order, to the
+    next tenth): a wave with all of a pair's tiles must not be further off. Added
+    up in the matrix cores from tile to tile it is: 3.87e-7, 2.14e-7, 2.71e-7,
+    1.96e-7, 3.47e-7 and 1.95e-7."""
+    print(f"error {hq}/{hkv} bs={bs} {dtype} B={batch} {lo}-{hi}", flush=True)
+    lens = np.rint(lo + (hi - lo) * (np.arange(batch) + 0.5) / batch).astype(int)
+    lens = np.random.default_rng(batch).permutation(lens)
+    cfg = synth.KVConfig("error", 1, hq, hkv, 128, dtype, bs, batch, ("uniform", 0, 0), 0.0, 4600)
+    w = Workload(cfg, lens=lens.tolist(), fill="device", staging_slots=1)
+    try:
+        dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+        out = w.new_out()
+        off = ref2 = 0.0
+        for seed in range(3):
+            g = torch.Generator(device="cuda")
+            g.manual_seed(seed)
+            flat = w.local_view.view(-1).view(dt)
+            flat.copy_(torch.randn(flat.numel(), generator=g, device="cuda"))
+            w.q.copy_(torch.randn(w.q.shape, generator=g, device="cuda"))
+            w.attention(0, out)
+            halves = flat.view(w.local_view.shape[0], 2, -1)
+            for b, n in enumerate(lens):
+                ids = torch.as_tensor(w.attn_tables[0][b, :-(-n // bs)], device="cuda")
+                k = halves[ids, 0].view(-1, hkv, bs, 128).permute(1, 0, 2, 3)
+                v = halves[ids, 1].view(-1, hkv, 128, bs).permute(1, 0, 3, 2)
+                k, v = (x.double().reshape(hkv, -1, 128)[:, :n].contiguous() for x in (k, v))
+                s = torch.matmul(w.q[b].double().view(hkv, -1, 128), k.transpose(1, 2).contiguous())
+                ref = torch.matmul(torch.softmax(s / 128 ** 0.5, dim=-1), v).reshape(-1, 128)
+                off += float((out[b].double() - ref).square().sum())
+                ref2 += float(ref.square().sum())
+        assert ema.slice_device_errors(w.h) == 0
+        assert (off / ref2) ** 0.5 <= bound, (off / ref2) ** 0.5
+    finally:
+        w.close()
+
+
 def test_several_id_lists_per_wave(ema):
     """80 sequences of about 4k tokens at 8 KV heads and block size 16: 80 tiles
     a wave, so its pieces go over several lists of 64 ids, 32 tiles each
