@@ -304,8 +304,9 @@ int ema_slice_reclaim(ema_slice_t h, int32_t n_blocks, int32_t* canon_tables, in
  * 1/sqrt(head_dim). out: device [batch][num_q_heads][head_dim] of out_dtype:
  * EMA_F32 (fp32 accumulation stored as is), or EMA_BF16 / EMA_F16 (the same
  * fp32 result rounded to nearest even).
- * The result does not depend on which local blocks hold the tokens, bit for
- * bit. Async on `stream`.
+ * The result does not depend on which local blocks hold the tokens or on how
+ * much wider than needed the table is, bit for bit (it does, in the last places,
+ * on the lengths of the other sequences in the batch). Async on `stream`.
  * Scheduling: stream-K over all (sequence, KV head) pairs when batch <= 4096
  * (2048 at 16 query heads per KV head), in the workspace allocated at create
  * (few pairs of short tables: one workgroup per pair, no workspace);

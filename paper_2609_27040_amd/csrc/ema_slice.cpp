@@ -808,12 +808,12 @@ int attention_call(ema_slice_t h, const void* q, const int32_t* block_table,
   float* part = nullptr;
   size_t part_rows = 0;
   if (noalloc) {
-    part_rows = size_t(2) * ema::attn_streamk_grid() * G;
+    part_rows = size_t(2) * ema::attn_streamk_grid() * ema::kMaxGroup;
     part = static_cast<float*>(h->noalloc_ws);
     a.info = reinterpret_cast<int32_t*>(static_cast<char*>(h->noalloc_ws) +
                                         ema::kNoAllocPartFloats * 4);
   } else if (stream_k) {
-    part_rows = size_t(2) * ema::attn_streamk_grid() * G;
+    part_rows = size_t(2) * ema::attn_streamk_grid() * ema::kMaxGroup;
     part = h->d_part;
     a.info = h->d_info;
   } else {

@@ -91,7 +91,8 @@ struct AttnArgs {
                             // by the direct form)
   int32_t* info;            // stream-K: [grid][2] combine records: pair that begins in a
                             // workgroup and goes on past it (-1: none), last workgroup that
-                            // holds it; or, of at most grid pairs, first (-1) and last workgroup
+                            // holds it; or, of at most grid pairs, first (-1: none, -2: a short
+                            // pair's runs) and last workgroup (number of runs)
   int32_t* err_count;
   const char* local;        // local pool base
   int64_t block_bytes;
@@ -121,6 +122,8 @@ constexpr int kMaxGroup = 16;          // query heads per KV head
 // current at the first call, at most kMaxStreamGrid. Partial slots: 2 per
 // workgroup, each kMaxGroup x (kHeadDim + 2) floats at most.
 int attn_streamk_grid();
+// With fewer query heads per KV head the same space holds more slots.
+constexpr int part_slots(int group, int grid) { return 2 * grid * (kMaxGroup / group); }
 
 // Fixed attention workspace for callers that cannot allocate: a file-scope
 // device array (one per GPU, held until the process ends) with partial slots

@@ -48,8 +48,8 @@
 //
 // Masked tokens (past the length, or in a block whose id is out of range) get
 // -inf scores and zeroed V, so NaN in unused slots never leaks. Reduction
-// orders depend only on sequence lengths and the table's width, not on block
-// ids.
+// orders depend only on the sequence lengths, not on block ids or the table's
+// width.
 #include "attn_store.h"
 #include "kernels.h"
 
@@ -71,16 +71,21 @@ constexpr int kWaves = 4;
 constexpr int kThreads = kWaves * 64;
 constexpr int kStreamWaves = 4;            // stream-K form
 constexpr int kStreamThreads = kStreamWaves * 64;
-constexpr int kDirectWaves = 8;            // direct form
+constexpr int kShortRuns = 8;              // of a short pair
+constexpr int kShortPair = -2;             // its combine record where each run left a partial
+constexpr int kDirectWaves = kShortRuns;   // direct form
 constexpr int kDirectThreads = kDirectWaves * 64;
 constexpr int kCombineWaves = 4;           // stream-K form's combine
-constexpr int kDirectPairs = 512;          // the most pairs it takes, and the longest, by the
-template <int BS>                          // width of the table (see attn_mfma_direct)
-constexpr int direct_tiles() { return BS >= 64 ? 8 : 16; }
 constexpr int kIt = 32;                    // tokens per tile (one wave iteration)
 constexpr int kPieceTiles = 32;            // tiles whose block ids are staged in LDS at once
 constexpr int kMaxIds = kPieceTiles * kIt / 16;
 constexpr int kGridChunkTiles = 32;        // tiles per workgroup in the grid fallback
+// Tokens of a short pair, in a batch of so many pairs (see attn_mfma_direct); 0:
+// no pair counts as short.
+template <int BS>
+__host__ __device__ constexpr int short_tokens(int64_t pairs) {
+  return pairs <= 256 && BS < 64 ? 2 * kShortRuns * kIt : pairs <= 512 ? kShortRuns * kIt : 0;
+}
 // Every pair a wave touches costs it about a tile's time beyond its tiles (the
 // result goes through LDS, new queries and block ids arrive); the stream-K
 // split counts it as kSegCost tiles. Measured, in us, for 0 / 1 / 2 / 3: an 8B
@@ -206,6 +211,7 @@ template <bool BF16, typename Next>
 __device__ __forceinline__ void consume_tile(Tile& T, const u32x4 (&qb)[4], float scale_log2,
                                              float& m, float& lsum, f32x4 (&o)[8],
                                              Next&& issue_next) {
+#pragma clang fp contract(off)   // the same roundings wherever this is inlined
   const int nv = T.nv;
   // Scores for tokens 8q4 + 4t + i of head r16.
   f32x4 s[2];
@@ -240,7 +246,7 @@ __device__ __forceinline__ void consume_tile(Tile& T, const u32x4 (&qb)[4], floa
     ph[q] = h0 | (h1 << 16);
     pl[q] = l0 | (l1 << 16);
   }
-  lsum = lsum * alpha + ps;
+  lsum = fmaf(lsum, alpha, ps);
   m = m_new;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {   // branch-free, so waits stay per tile
@@ -253,7 +259,6 @@ __device__ __forceinline__ void consume_tile(Tile& T, const u32x4 (&qb)[4], floa
   const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int n0 = 0; n0 < 8; n0 += 4) {
-#pragma clang fp contract(off)
     f32x4 t[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -682,12 +687,125 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
   return x;
 }
 
+// Short pairs are cut into kShortRuns equal runs of one or two tiles whatever
+// else is in the batch, whose partials are merged in one go, in order. The direct
+// form and the stream-K form both take them this way, so that a batch's result
+// does not depend on which of the two it gets.
+struct ShortCut {
+  int per, n;         // tiles of a run, runs
+  __device__ __forceinline__ explicit ShortCut(int nt)
+      : per((nt + kShortRuns - 1) / kShortRuns), n((nt + per - 1) / per) {}
+};
+
+// Run `run` of the pair in g (b, kvh, len and nt are set) by one wavefront; its
+// partial goes to sink(m, lsum, o).
+template <int G, int BS, bool BF16, typename Sink>
+__device__ __forceinline__ void attend_run(const AttnArgs& a, Group g, const ShortCut& cut, int run,
+                                           int lane, Sink&& sink) {
+  static_assert(short_tokens<BS>(1) <= 2 * kShortRuns * kIt, "a run is one or two tiles");
+  const int r16 = lane & 15, q4 = lane >> 4;
+  g.j0 = run * cut.per;
+  g.j1 = min(g.nt, g.j0 + cut.per);
+  first_group<BS>(g);
+  const int32_t got = load_group_ids<BS>(a, g, lane);
+  u32x4 qb[4];
+  load_q<G>(qb, a, g.b, g.kvh, r16, q4);
+  const int32_t ids = check_group_ids<BS>(a, g, lane, got);
+  Tile A, B;
+  load_tile_ids<BS>(A, a, g, ids, g.j0, r16, q4);
+  mask_q<G>(qb, qb, r16);
+  float m = -INFINITY, lsum = 0.0f;
+  f32x4 o[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) o[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const bool two = g.j1 - g.j0 == 2;
+  consume_tile<BF16>(A, qb, a.scale_log2, m, lsum, o, [&] {
+    if (two) load_tile_ids<BS>(B, a, g, ids, g.j0 + 1, r16, q4);
+  });
+  if (two) consume_tile<BF16>(B, qb, a.scale_log2, m, lsum, o, [] {});
+  sink(m, lsum, o);
+}
+
+// A short pair by one workgroup of Waves wavefronts, merged in LDS.
+template <int G, int BS, bool BF16, int Waves>
+__device__ __forceinline__ void attend_short(const AttnArgs& a, int b, int kvh, int len,
+                                             Part<G>* parts) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));             // as in write_pair: not kept from pair to pair
+  const int lane = tid & 63;
+  const int64_t row = int64_t(b) * a.q_heads + kvh * G;
+  constexpr int kItems = G * (kD / 4);
+  if (len == 0) {
+    for (int e = tid; e < kItems; e += Waves * 64)
+      store_out4(a, row * kD + 4 * e, out_f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+    return;
+  }
+  Group g;
+  g.b = b;
+  g.kvh = kvh;
+  g.len = len;
+  g.nt = (len + kIt - 1) / kIt;
+  const ShortCut cut(g.nt);
+  for (int run = uniform(tid >> 6); run < cut.n; run += Waves)
+    attend_run<G, BS, BF16>(a, g, cut, run, lane, [&](float m, float lsum, const f32x4 (&o)[8]) {
+      put_part<G>(parts[run], m, lsum, o, lane & 15, lane >> 4);
+    });
+  __syncthreads();
+  for (int e = tid; e < kItems; e += Waves * 64) {
+    const int h = e / (kD / 4), d4 = e % (kD / 4);
+    float M, L;
+    f32x4 O;
+    merge_parts<G, kShortRuns, 1>(parts, 0, 1, cut.n, h, d4, M, L, O);
+    write_row4(a, row + h, d4, L, O);
+  }
+}
+
+// Run `run` of a short pair by one wavefront of the stream-K form: its partial
+// goes to slot kShortRuns * pair + run, and the first run's wavefront leaves the
+// pair's record (kShortPair, number of runs).
+template <int G, int BS, bool BF16>
+__device__ __forceinline__ void attend_short_run(const AttnArgs& a, int pair, int run, int b, int kvh,
+                                                 int len, Part<G>& part, int lane) {
+  constexpr int kItems = G * (kD / 4);
+  if (len == 0) {
+    if (run == 0) {
+      for (int e = lane; e < kItems; e += 64)
+        store_out4(a, (int64_t(b) * a.q_heads + kvh * G) * kD + 4 * e,
+                   out_f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+      if (lane == 0) a.info[2 * pair] = -1;
+    }
+    return;
+  }
+  Group g;
+  g.b = b;
+  g.kvh = kvh;
+  g.len = len;
+  g.nt = (len + kIt - 1) / kIt;
+  const ShortCut cut(g.nt);
+  if (run == 0 && lane == 0) {
+    a.info[2 * pair] = kShortPair;
+    a.info[2 * pair + 1] = cut.n;
+  }
+  if (run >= cut.n) return;
+  attend_run<G, BS, BF16>(a, g, cut, run, lane, [&](float m, float lsum, const f32x4 (&o)[8]) {
+    put_part<G>(part, m, lsum, o, lane & 15, lane >> 4);
+  });
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  for (int e = lane; e < kItems; e += 64) {
+    const int h = e / (kD / 4), d4 = e % (kD / 4);
+    write_partial4<G>(a, kShortRuns * pair + run, h, d4, part.m[h], part.l[h],
+                      *reinterpret_cast<const f32x4*>(&part.o[h][4 * d4]));
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
 // Combine records of the stream-K form: one per workgroup (the pair that begins
 // there and goes on past it, its last workgroup), or one per pair (its first and
 // last workgroup) where there are no more pairs than workgroups, so that few
 // pairs take a combine of few workgroups (3 sequences of 100-900 tokens at 8
 // heads to each of 8 KV heads: 12.2 -> 11.4 us a call). First value -1: nothing
-// to combine.
+// to combine. kShortPair (by pair only): the second is the number of the pair's
+// runs, whose partials are in slots kShortRuns * pair on.
 __host__ __device__ __forceinline__ bool records_by_pair(const AttnArgs& a, int64_t grid) {
   return int64_t(a.batch) * a.kv_heads <= grid;
 }
@@ -702,7 +820,8 @@ __host__ __device__ __forceinline__ bool records_by_pair(const AttnArgs& a, int6
 // written, one that crosses a workgroup boundary leaves one partial in global
 // memory -- slot 2w for the pair workgroup w entered in its middle, 2w + 1 for
 // the one that begins there and goes on -- and a record, written by the
-// workgroup it begins in, for the combine.
+// workgroup it begins in, for the combine. Batches that the direct form would
+// take, were their table no wider than they need, are cut as it cuts them.
 template <int G, int BS, bool BF16>
 // Compiled as if two workgroups shared a CU (at most 256 registers a lane),
 // although one per CU is launched: under the looser bound the compiler's
@@ -710,7 +829,7 @@ template <int G, int BS, bool BF16>
 // 11-12 % slower.
 __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs a) {
   __shared__ int32_t s_len[streamk_max_batch(G)];
-  __shared__ int32_t s_total[kStreamWaves];
+  __shared__ int2 s_total[kStreamWaves];          // units of the wave's sequences, any of them long
   __shared__ int32_t s_start[kStreamWaves][2];   // first sequence of each wave's range, units into it
   __shared__ Part<G> s_part[kStreamWaves][2];    // head, tail
   __shared__ int4 s_open[kStreamWaves];   // head pair (-1: none), whether it ends in this
@@ -734,6 +853,8 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
     return nt > 0 ? (nt + kSegCost) * H : 0;
   };
   int total = 0;
+  const int at_most = short_tokens<BS>(int64_t(B) * H);
+  bool longer = at_most == 0;
   for (int c = b0; c < b1; c += 4) {
     int raw[4];
 #pragma unroll
@@ -744,21 +865,44 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
       const int len = clamp_len(raw[i], a);
       if (blockIdx.x == 0 && len != raw[i] && raw[i] > 0) atomicAdd(a.err_count, 1);
       s_len[c + i] = len;
+      longer |= len > at_most;
       total += units_of(len);
     }
   }
   const int incl = wave_inclusive_sum(total);
-  if (lane == 63) s_total[wave] = incl;
+  const bool any_longer = __ballot(longer) != 0;
+  if (lane == 63) s_total[wave] = int2{incl, any_longer};
   if (tid < kStreamWaves) s_start[tid][0] = -1;
   __syncthreads();
-  int before = incl - total, U = 0;
+  const int n_waves = int(gridDim.x) * kStreamWaves;
+  int before = incl - total, U = 0, long_ones = 0;
 #pragma unroll
   for (int w = 0; w < kStreamWaves; ++w) {
-    const int t = s_total[w];
-    if (w < wave) before += t;
-    U += t;
+    const int2 t = s_total[w];
+    if (w < wave) before += t.x;
+    U += t.x;
+    long_ones |= t.y;
   }
-  const int n_waves = int(gridDim.x) * kStreamWaves;
+  if (uniform(long_ones) == 0) {   // few short pairs, in a table too wide for the direct form
+    if (2 * B * H <= int(gridDim.x) && B * H * kShortRuns <= part_slots(G, int(gridDim.x))) {
+      // a slot for each run, the runs spread over all workgroups
+      for (int id = wave * int(gridDim.x) + int(blockIdx.x); id < B * H * kShortRuns;
+           id += n_waves) {
+        const int pair = id / kShortRuns, b = pair / H;
+        attend_short_run<G, BS, BF16>(a, pair, id % kShortRuns, b, pair - b * H, uniform(s_len[b]),
+                                      s_part[wave][0], lane);
+      }
+      return;
+    }
+    for (int p = blockIdx.x; p < B * H; p += gridDim.x) {
+      const int b = p / H;
+      attend_short<G, BS, BF16, kStreamWaves>(a, b, p - b * H, uniform(s_len[b]), &s_part[0][0]);
+      __syncthreads();
+      if (by_pair && tid == 0) a.info[2 * p] = -1;
+    }
+    if (!by_pair && tid == 0) a.info[2 * blockIdx.x] = -1;
+    return;
+  }
   const int per = (U + n_waves - 1) / n_waves;
   const int first_wave = int(blockIdx.x) * kStreamWaves;
   // the thread whose sequences hold a wave's first unit says so
@@ -894,60 +1038,33 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
 }
 
 // Direct form, for few pairs that are short by the table's width: one
-// workgroup of eight wavefronts per (sequence, KV head), each streaming an
-// equal run of the pair's tiles, merged in LDS. No plan over all lengths and
-// no combine: one launch, and what it takes is the chain length - block id -
-// tile - merge. Against stream-K, 4 query heads to each of 8 KV heads, block
-// size 16, us a call: 8 pairs of up to 256 tokens 9.8 / 6.8, up to 512 9.7 / 7.5,
-// up to 1024 10.2 / 10.3; 256 pairs 12.9 / 7.6, 16.1 / 11.8, 21.4 / 19.3; 512
-// pairs 17.0 / 14.1, 22.4 / 21.0, 33.9 / 35.0; 1024 pairs 24.1 / 24.7, 34.9 /
-// 37.6. Block size 64: 32 pairs 9.9 / 7.3, 10.9 / 11.0; 512 pairs 18.1 / 14.3,
-// 24.4 / 25.3 -- hence up to 512 pairs, of 512 tokens, or 256 from block size 64
-// on (two tiles and one tile a wave).
+// workgroup of eight wavefronts per (sequence, KV head), a run of the pair's
+// tiles each, merged in LDS. No plan over all lengths and no combine: one
+// launch, and what it takes is the chain length - block id - tile - merge.
+// Against stream-K, 4 query heads to each of 8 KV heads, block size 16, us a
+// call: 8 pairs of up to 256 tokens 9.6 / 6.2, up to 512 9.4 / 8.9, up to 1024
+// 10.2 / 10.3; 256 pairs 13.5 / 8.7, 17.9 / 13.7, 21.4 / 19.3; 512 pairs 17.5 /
+// 15.3, 24.1 / 24.0, 33.9 / 35.0; 1024 pairs of up to 256 24.1 / 24.7. At 1, 2 and
+// 8 heads the same within 5 %, at 16 more for the direct form (256 pairs 17.9 /
+// 9.9, 21.8 / 14.8). Block size 64, 32 pairs 9.9 / 7.3, up to 512 tokens 10.9 /
+// 11.0, 512 pairs 18.1 / 14.3 and 24.4 / 25.3.
+// Short pairs in a table too wide for it take a plan and, where their runs are
+// spread over the workgroups, the combine, but are cut the same way. Then, 4
+// heads, block size 16, stream-K's own ranges / one workgroup to a pair / the runs
+// spread: 8 pairs of up to 128 tokens 9.6 / 7.2 / 8.0, 256 9.6 / 9.2 / 8.1, 512 9.4
+// / 12.8 / 9.3; 64 pairs 10.6 / 7.9 / 8.7, 10.7 / 10.6 / 9.0, 11.3 / 14.8 / 10.7; 256
+// pairs 12.5 / 8.2 / 13.4, 13.5 / 11.4 / 14.5, 17.9 / 16.4 / 19.1; 512 pairs 15.1 /
+// 12.5, 17.5 / 18.7 and 24.1 / 28.1 -- hence one or two tiles a run up to 256 pairs
+// and one tile up to 512, runs spread up to one pair to two workgroups.
 template <int G, int BS, bool BF16>
 __global__ __launch_bounds__(kDirectThreads, 2) void attn_mfma_direct(AttnArgs a) {
-  __shared__ Part<G> s_part[kDirectWaves];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = uniform(tid >> 6);
+  __shared__ Part<G> s_part[kShortRuns];
   const int kvh = blockIdx.x;
   const int b = blockIdx.y;
-  const int64_t row = int64_t(b) * a.q_heads + kvh * G;
   const int raw = a.seq_lens[b];
   const int len = clamp_len(raw, a);
-  if (kvh == 0 && tid == 0 && len != raw && raw > 0) atomicAdd(a.err_count, 1);
-  constexpr int kItems = G * (kD / 4);
-  if (len == 0) {
-    for (int e = tid; e < kItems; e += kDirectThreads)
-      store_out4(a, row * kD + 4 * e, out_f32x4{0.0f, 0.0f, 0.0f, 0.0f});
-    return;
-  }
-  const int nt = (len + kIt - 1) / kIt;
-  const int per = (nt + kDirectWaves - 1) / kDirectWaves;
-  Group g;
-  g.b = b;
-  g.kvh = kvh;
-  g.len = len;
-  g.nt = nt;
-  g.j0 = min(nt, wave * per);
-  g.j1 = min(nt, g.j0 + per);
-  if (g.j0 < g.j1) {
-    first_group<BS>(g);
-    stream_wave<G, BS, BF16>(
-        a, g, [](Group& n) { return next_in_segment<BS>(n); },
-        [&](const Group&, float m, float lsum, const f32x4 (&o)[8]) {
-          put_part<G>(s_part[wave], m, lsum, o, lane & 15, lane >> 4);
-        });
-  }
-  __syncthreads();
-  const int n = (nt + per - 1) / per;
-  for (int e = tid; e < kItems; e += kDirectThreads) {
-    const int h = e / (kD / 4), d4 = e % (kD / 4);
-    float M, L;
-    f32x4 O;
-    merge_parts<G, kDirectWaves, 1>(s_part, 0, 1, n, h, d4, M, L, O);
-    write_row4(a, row + h, d4, L, O);
-  }
+  if (kvh == 0 && threadIdx.x == 0 && len != raw && raw > 0) atomicAdd(a.err_count, 1);
+  attend_short<G, BS, BF16, kDirectWaves>(a, b, kvh, len, s_part);
 }
 
 // Grid form for batches too large for the LDS work list: grid (chunk of
@@ -997,11 +1114,18 @@ struct Partials {
   __device__ __forceinline__ void load(const AttnArgs& a, int w0, int i0, int w_max, int g, int d4) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int64_t slot = 2 * int64_t(min(w0 + i0 + k, w_max)) + (i0 + k == 0 ? 1 : 0);
-      m[k] = a.part_ml[(slot * G + g) * 2];
-      l[k] = a.part_ml[(slot * G + g) * 2 + 1];
-      o[k] = *reinterpret_cast<const f32x4*>(&a.part_o[(slot * G + g) * kD + 4 * d4]);
+      get(k, a, 2 * int64_t(min(w0 + i0 + k, w_max)) + (i0 + k == 0 ? 1 : 0), g, d4);
     }
+  }
+  // The first n <= K of a short pair's: slot, slot + 1, ...
+  __device__ __forceinline__ void load_short(const AttnArgs& a, int slot, int n, int g, int d4) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) get(k, a, slot + min(k, n - 1), g, d4);
+  }
+  __device__ __forceinline__ void get(int k, const AttnArgs& a, int64_t slot, int g, int d4) {
+    m[k] = a.part_ml[(slot * G + g) * 2];
+    l[k] = a.part_ml[(slot * G + g) * 2 + 1];
+    o[k] = *reinterpret_cast<const f32x4*>(&a.part_o[(slot * G + g) * kD + 4 * d4]);
   }
   // Merges the first n of them into the running (M, L, O).
   __device__ __forceinline__ void merge(int n, float& M, float& L, f32x4& O) {
@@ -1050,8 +1174,9 @@ __global__ __launch_bounds__(kCombineWaves * 64) void attn_combine_streamk(AttnA
   const int pair = by_pair ? int(blockIdx.x) : rec;
   const int wave = uniform(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int n = last_wg - w0 + 1;
-  if (rec < 0 || (wave > 0 && n <= 4)) return;
+  const bool whole_runs = by_pair && rec == kShortPair;   // of a short pair
+  const int n = whole_runs ? 1 : last_wg - w0 + 1;
+  if ((rec < 0 && !whole_runs) || (wave > 0 && n <= 4)) return;
   // G = 1: the upper half of the lanes repeats the lower half's work
   const int e = (blockIdx.y * 64 + lane) % (G * (kD / 4));
   const int g = e / (kD / 4), d4 = e % (kD / 4);
@@ -1059,7 +1184,11 @@ __global__ __launch_bounds__(kCombineWaves * 64) void attn_combine_streamk(AttnA
   f32x4 O = {0.0f, 0.0f, 0.0f, 0.0f};
   const int per = n <= 4 ? n : (n + kCombineWaves - 1) / kCombineWaves;
   const int i1 = min(n, (wave + 1) * per);
-  if (per <= 4) {
+  if (whole_runs) {
+    Partials<G, kShortRuns> p;
+    p.load_short(a, kShortRuns * pair, last_wg, g, d4);
+    p.merge(last_wg, M, L, O);
+  } else if (per <= 4) {
     Partials<G, 4> p;
     p.load(a, w0, min(wave * per, n - 1), last_wg, g, d4);
     p.merge(i1 - wave * per, M, L, O);
@@ -1099,8 +1228,9 @@ __global__ __launch_bounds__(kCombineWaves * 64) void attn_combine_streamk(AttnA
 
 template <int G, int BS, bool BF16>
 hipError_t launch_typed(const AttnArgs& a, hipStream_t stream) {
-  if (a.stream_k && int64_t(a.max_blocks) * BS <= direct_tiles<BS>() * kIt &&
-      int64_t(a.batch) * a.kv_heads <= kDirectPairs) {
+  const int64_t pairs = int64_t(a.batch) * a.kv_heads;
+  if (a.stream_k && short_tokens<BS>(pairs) > 0 &&
+      int64_t(a.max_blocks) * BS <= short_tokens<BS>(pairs)) {
     hipLaunchKernelGGL((attn_mfma_direct<G, BS, BF16>), dim3(a.kv_heads, a.batch),
                        dim3(kDirectThreads), 0, stream, a);
     return hipGetLastError();

@@ -97,10 +97,11 @@ def test_partials_of_one_pair(ema, hq, others, tiles):
 
 
 @pytest.mark.parametrize("hq,hkv,bs,dtype,batch,width", [
-    (8, 8, 16, "f16", 8, 32), (32, 8, 16, "bf16", 64, 32), (4, 1, 32, "bf16", 512, 16),
+    (8, 8, 16, "f16", 8, 32), (32, 8, 16, "bf16", 64, 32), (4, 1, 32, "bf16", 256, 16),
     (16, 1, 64, "f16", 3, 4), (6, 3, 128, "bf16", 5, 2), (4, 2, 256, "bf16", 4, 1),
-    # one past each line of the rule: 513 pairs, 17 tiles, 9 tiles
-    (2, 1, 16, "bf16", 513, 32), (4, 2, 32, "f16", 4, 17), (8, 1, 64, "bf16", 4, 5)])
+    (16, 8, 16, "f16", 64, 16),
+    # one past each line of the rule: 257 pairs, 513 pairs, 17 tiles, 9 tiles
+    (2, 1, 16, "bf16", 257, 32), (1, 1, 16, "f16", 513, 16), (4, 2, 32, "f16", 4, 17), (8, 1, 64, "bf16", 4, 5)])
 def test_short_tables(ema, hq, hkv, bs, dtype, batch, width):
     """Both sides of the line between the direct and the stream-K form: lengths
     from 0 to the table's width, ids outside the pool, and the same outputs
@@ -191,6 +192,46 @@ def test_error_against_64_bits(ema, hq, hkv, bs, dtype, batch, lo, hi, bound):
                 ref2 += float(ref.square().sum())
         assert ema.slice_device_errors(w.h) == 0
         assert (off / ref2) ** 0.5 <= bound, (off / ref2) ** 0.5
+    finally:
+        w.close()
+
+
+@pytest.mark.parametrize("hq,hkv,bs,dtype,batch,longest", [
+    (8, 8, 16, "f16", 8, 512), (32, 8, 16, "bf16", 32, 500), (1, 1, 128, "f16", 200, 200),
+    (4, 2, 64, "bf16", 20, 256), (4, 4, 32, "f16", 1, 40),
+    # pairs whose runs just have a slot each in the workspace, and one more
+    (8, 1, 16, "bf16", 128, 300), (8, 1, 32, "bf16", 129, 512), (32, 2, 256, "bf16", 32, 256),
+    (16, 1, 16, "f16", 65, 512),
+    (32, 8, 16, "bf16", 64, 256), (1, 1, 256, "bf16", 257, 256),
+    # past the rule by a pair or a token, and long
+    (2, 1, 16, "bf16", 257, 512), (2, 1, 32, "f16", 300, 257), (2, 1, 64, "f16", 513, 256), (4, 2, 32, "f16", 9, 513), (8, 1, 64, "bf16", 4, 257),
+    (16, 4, 16, "bf16", 30, 3000)])
+def test_wider_tables_give_the_same_bits(ema, hq, hkv, bs, dtype, batch, longest):
+    """One batch through tables just wide enough and wider ones, on both sides
+    of the direct form's line."""
+    print(f"widths {hq}/{hkv} bs={bs} B={batch} {longest}", flush=True)
+    rng = np.random.default_rng(longest + batch)
+    lens = rng.integers(0, longest + 1, batch)
+    lens[batch // 2], lens[0] = 0, longest
+    cfg = synth.KVConfig("widths", 1, hq, hkv, 128, dtype, bs, batch, ("uniform", 0, 0), 0.0, 4700)
+    w = Workload(cfg, lens=lens.tolist(), staging_slots=1)
+    try:
+        width = w.attn_dev.shape[2]
+        out = w.new_out()
+        w.attention(0, out)
+        for more in (1, 40, 1000):
+            table = torch.full((batch, width + more), -1, dtype=torch.int32, device="cuda")
+            table[:, :width] = w.attn_dev[0]
+            for call in (ema.paged_decode_attention, ema.paged_decode_attention_noalloc):
+                wide = w.new_out()
+                wide.fill_(float("nan"))
+                call(w.h, w.q, table, w.lens_dev, wide)
+                assert torch.equal(out, wide), (more, call.__name__)
+        assert ema.slice_device_errors(w.h) == 0
+        st = oracle_mirror(w)
+        ref = oracle.paged_decode_attention(w.q16, w.attn_tables[0], w.lens, st.read_block, w.hkv,
+                                            w.D, w.bs, w.cfg.dtype)
+        assert rel_err(out.cpu().numpy(), ref) <= TOL
     finally:
         w.close()
 
