@@ -107,3 +107,25 @@ def test_same_layout_rounds(ema, H, bs, n):
         assert ema.slice_device_errors(p.h) == 0
     finally:
         p.close()
+
+
+def test_lists_longer_than_a_grid_row(ema):
+    """A same-layout list past 32768 blocks, the list kernel's second grid
+    layer: every block lands where it should, and ids out of range on both
+    sides of the line leave their destinations alone."""
+    n = 32768 + 6
+    print(f"long list n={n}", flush=True)
+    p = Pools(ema, 1, 16, synth.LAYOUT_ATTN, n, n)
+    try:
+        rng = np.random.default_rng(5)
+        src, dst = n + rng.permutation(n), rng.permutation(n)
+        bad = {0: -1, 32767: 2 * n, 32768: 2 ** 31 - 1, n - 1: -2 ** 31}
+        for i, u in bad.items():
+            (src if i % 2 else dst)[i] = u
+        p.run(src, dst)
+        ok = np.array([i for i in range(n) if i not in bad])
+        p.host[0][dst[ok]] = p.host[1][src[ok] - n]
+        p.check()
+        assert ema.slice_device_errors(p.h) == len(bad)
+    finally:
+        p.close()

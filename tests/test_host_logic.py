@@ -193,6 +193,64 @@ def test_library_run_prefetch_validation_host_only():
         lib.close()
 
 
+@pytest.mark.parametrize("n_local,n", [(200000, 3), (200000, 186), (200000, 187), (200000, 400),
+                                       (40, 3), (0, 3)])
+def test_id_sets_of_any_pool_and_list_size(n_local, n):
+    """Rejections by the sets that free and the copy lists collect ids in: few
+    ids of a large pool go to a hash set, others to a bitmap (from 187 ids of
+    191000 blocks on) with a hash set for ids outside the pools. Ids at both ends
+    of both pools, and the order of the checks: duplicates and overlaps come
+    before ranges and owners."""
+    from paper_2609_27040_amd import ema
+    bb = 2 * 16 * 1 * 128 * 2
+    if n_local == 200000:
+        n_local, n_slice = 95000, 96000
+        assert (n <= 186) == ((n_local + n_slice) // 64 > 16 * n)
+    else:
+        n_slice = 8
+    h = ema.slice_create(1, 128, 16, "bf16", 0, n_local * bb, n_slice * bb, host_only=True)
+    total = n_local + n_slice
+
+    def refused(code, call, *args):
+        with pytest.raises(ema.EmaError) as e:
+            call(h, *args)
+        assert e.value.code == code
+        return str(e.value)
+    try:
+        if n_local:
+            stage = ema.slice_alloc_blocks(h, ema.POOL_LOCAL, [ema.STAGING] * n_local)
+        away = ema.slice_alloc_blocks(h, ema.POOL_SLICE, [5] * n_slice)
+        ends = [int(away[-1]), int(away[0])] + ([int(stage[0])] if n_local else [])
+        ids = np.array((ends + [int(u) for u in away[1:-1]])[:n])
+        for dup in (ids[0], ids[-1]):
+            assert "duplicate" in refused(ema.ERR_INVAL, ema.slice_free_blocks, np.append(ids, dup))
+        for bad in (-1, total, 2 ** 31 - 1, -2 ** 31):
+            assert "range" in refused(ema.ERR_INVAL, ema.slice_free_blocks, np.append(ids, bad))
+            assert "duplicate" in refused(ema.ERR_INVAL, ema.slice_free_blocks,
+                                          np.concatenate([[bad], ids, [bad]]))
+        if n_local:
+            k = min(n, n_local, n_slice)
+            src, dst = away[-k:], stage[:k]
+            ema.slice_prefetch(h, src, dst)
+            for i in (0, k - 1):
+                twice, both, out = dst.copy(), src.copy(), dst.copy()
+                twice[i] = dst[(i + 1) % k]
+                assert "duplicate" in refused(ema.ERR_INVAL, ema.slice_prefetch, src, twice)
+                both[i] = dst[(i + 1) % k]
+                assert "overlap" in refused(ema.ERR_INVAL, ema.slice_prefetch, both, dst)
+                for bad in (-1, total, 2 ** 31 - 1):
+                    out[i] = bad
+                    assert "range" in refused(ema.ERR_INVAL, ema.slice_prefetch, src, out)
+                    both[i] = bad
+                    assert "overlap" in refused(ema.ERR_INVAL, ema.slice_prefetch, both, out)
+        assert ema.slice_get_info(h)["free_slice"] == 0        # nothing was freed
+        ema.slice_free_blocks(h, ids)
+        assert ema.slice_get_info(h)["free_slice"] == int((ids >= n_local).sum())
+        refused(ema.ERR_OWNER, ema.slice_free_blocks, ids[-1:])
+    finally:
+        ema.slice_destroy(h)
+
+
 def test_binding_refuses_arrays_the_kernels_could_not_read():
     """Device entry points take GPU tensors only: the binding refuses host
     arrays, CPU tensors, other dtypes, non-contiguous views and short inputs

@@ -168,6 +168,9 @@ class StressRun:
                 dst_t = torch.as_tensor(back.astype(np.int32), device="cuda")
                 _, mms, _, _ = self.timer.time(
                     self.s, lambda: ema.slice_migrate(w.h, src_t, dst_t, stream=self.s))
+                bpick = self._sample(len(cur))
+                rec["exact"] = rec["exact"] and self._same_content(
+                    self._rows(cur[bpick]), cur[bpick], self._rows(back[bpick]), back[bpick])
                 ema.slice_free_blocks(w.h, cur)
                 tables[pos[:, 0], pos[:, 1], pos[:, 2]] = back
                 w.tables_dev.copy_(torch.from_numpy(tables.astype(np.int32)))
