@@ -338,8 +338,8 @@ int ema_paged_decode_attention(ema_slice_t h, const void* q, const int32_t* bloc
  * ordered by the caller. Nothing in it needs clearing: each call writes every
  * record it reads.
  * Limits: batch <= 4096 (2048 at 16 query heads per KV head),
- * batch * num_kv_heads <= 32768, at most 512 compute units; beyond them the
- * call returns INVAL and does nothing. Other errors as for
+ * batch * num_kv_heads <= 32768 (an interface limit only), at most 512 compute
+ * units; beyond them the call returns INVAL and does nothing. Other errors as for
  * ema_paged_decode_attention.
  */
 int ema_paged_decode_attention_noalloc(ema_slice_t h, const void* q, const int32_t* block_table,

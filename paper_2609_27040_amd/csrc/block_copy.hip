@@ -11,7 +11,8 @@
 // steadier for them. In lists of scattered blocks above 64 KiB a block's pieces,
 // up to 256 KiB of them, are dealt to one XCD (see xcd_item); ascending runs
 // keep their order (dealt, a reclaim of 5 % moved 5.65-5.95 TB/s instead of
-// 6.0-6.3).
+// 6.0-6.3). In order, 512 MiB take 176 us in one run and 165 in 20, at any block
+// size from 64 KiB; with pieces numbered in 64 bits one run took 0.3-0.8 % less.
 //
 // Otherwise blocks change layout. K rows (256 bytes) only change order, V is
 // transposed between [token][channel] (NHD) and [channel][token] (ATTN) in
@@ -243,7 +244,8 @@ __global__ __launch_bounds__(256) void block_copy_kernel(PoolView pv, CopyIds id
     // the lanes of channels 2k and 2k + 1 (lane ^ 2) trade four tokens, so that
     // each holds both channels of four tokens and scatters them into the
     // [token][channel] tile as whole words; then write 16 whole 256-B token
-    // rows.
+    // rows. (8192 blocks of 64 KiB 210 us; in single channels, twice the LDS
+    // writes, 213, but up to 16 blocks 3.0 instead of 3.2.)
     u32x4 v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -452,9 +454,10 @@ __global__ __launch_bounds__(256) void block_copy_same_kernel(PoolView pv, CopyI
 // gives piece and block, so nothing is divided, and the few arguments come in
 // one load: a wavefront lives only for its ids, its two loads and its two
 // stores, and how long it lives sets how many bytes a CU keeps in flight.
-// 9801 blocks of 64 KiB take 207.7 us (6.18 TB/s); with one more division and
-// the general kernel's arguments 209.6, with four wavefronts to a workgroup
-// 6.02 TB/s.
+// Against the same with one more division and the general kernel's arguments, in
+// us: 64 blocks of 64 KiB 3.49 / 3.31, 256 8.1 / 7.7, 1024 28.1 / 27.8, 9801 209.0 /
+// 207.5 (6.19 TB/s); blocks of 8 KiB, 64 2.67 / 2.45, 1024 6.1 / 6.3, 10000 34.8 /
+// 34.7. With four wavefronts to a workgroup 9801 go at 6.02 TB/s.
 constexpr int kListRows = 32768;
 __global__ __launch_bounds__(64) void block_copy_list_kernel(
     char* local, char* slice, const int32_t* __restrict__ src, const int32_t* __restrict__ dst,

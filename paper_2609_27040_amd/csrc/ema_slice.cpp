@@ -5,8 +5,9 @@
 // upload area for the plans and copy lists that reclaim and run prefetches
 // build on the host (with its pinned host staging, sized for the largest
 // plan), and the stream-K attention workspace (partials and combine records of
-// every workgroup). Only the grid form of attention (batches above the stream-K limit, or EMA_CREATE_ATTN_GRID) grows
-// a workspace on first use; growing synchronizes the device.
+// every workgroup). Only the grid form of attention (batches above the stream-K
+// limit, or EMA_CREATE_ATTN_GRID) grows a workspace on first use; growing
+// synchronizes the device.
 #include "ema_slice.h"
 
 #include <hip/hip_runtime.h>
@@ -740,7 +741,7 @@ int ema_slice_reclaim(ema_slice_t h, int32_t n_blocks, int32_t* canon_tables, in
 
 namespace {
 
-// Both attention entry points. `noalloc`: stream-K only, in the fixed
+// Both attention entry points. `noalloc`: never the grid form, in the fixed
 // per-device workspace, no host validation (checked mode reads arrays back)
 // and nothing that allocates.
 int attention_call(ema_slice_t h, const void* q, const int32_t* block_table,
@@ -785,8 +786,10 @@ int attention_call(ema_slice_t h, const void* q, const int32_t* block_table,
   }
   // Scheduling: stream-K (equal tile ranges, one workgroup per CU, at most two
   // partials each; workspace allocated at create) when the batch fits its LDS
-  // work list, else a grid of 1024-token chunks with one partial per
-  // (sequence, head, chunk) in a workspace that grows on first use.
+  // work list -- few pairs of short tables then go one workgroup to a pair
+  // without a workspace, which the launch decides -- else a grid of 1024-token
+  // chunks with one partial per (sequence, head, chunk) in a workspace that
+  // grows on first use.
   const int64_t tiles = int64_t(batch) * hkv * ((max_tokens + 31) / 32);
   const bool fits_streamk = batch <= ema::streamk_max_batch(G) && tiles < (int64_t(1) << 30);
   if (noalloc) {

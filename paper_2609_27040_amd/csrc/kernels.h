@@ -130,7 +130,8 @@ constexpr int part_slots(int group, int grid) { return 2 * grid * (kMaxGroup / g
 // for up to kNoAllocGrid stream-K workgroups at kMaxGroup query heads per KV
 // head, followed by their combine records. Every call writes each record it
 // reads, so nothing in it needs clearing; calls that overlap on one GPU race on
-// it. The entry point takes up to kNoAllocPairs (sequence, KV head) pairs.
+// it. The entry point takes up to kNoAllocPairs (sequence, KV head) pairs: a
+// limit of its interface, as the space needed no longer grows with them.
 constexpr int kNoAllocGrid = 512;
 constexpr int kNoAllocPairs = 32768;
 constexpr size_t kNoAllocPartFloats = size_t(2) * kNoAllocGrid * kMaxGroup * (kHeadDim + 2);

@@ -90,7 +90,10 @@ __host__ __device__ constexpr int short_tokens(int64_t pairs) {
 // result goes through LDS, new queries and block ids arrive); the stream-K
 // split counts it as kSegCost tiles. Measured, in us, for 0 / 1 / 2 / 3: an 8B
 // layer 112.1 / 112.0 / 111.8 / 111.4, a 70B share 44.2 / 43.0 / 43.1 / 43.0,
-// 512 sequences of 17-1000 tokens 204 / 181 / 180 / 182.
+// 512 sequences of 17-1000 tokens 204 / 181 / 180 / 182. At 16 query heads to
+// each of 8 KV heads, whose partials are four times larger, for 1 / 2 / 4 / 8: 256
+// sequences of 17-1000 tokens 109 / 102 / 104 / 108, 512 of them 210 / 201 / 205 /
+// 215, 64 of 500-4000 104.2 / 103.6 / 105.2 / 105.1.
 constexpr int kSegCost = 2;
 
 __device__ __forceinline__ u32x4 ld16(const char* p) {
