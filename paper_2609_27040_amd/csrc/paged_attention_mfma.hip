@@ -82,9 +82,8 @@ constexpr int kMaxIds = kPieceTiles * kIt / 16;
 constexpr int kGridChunkTiles = 32;        // tiles per workgroup in the grid fallback
 // Tokens of a short pair, in a batch of so many pairs (see attn_mfma_direct); 0:
 // no pair counts as short.
-template <int BS>
 __host__ __device__ constexpr int short_tokens(int64_t pairs) {
-  return pairs <= 256 && BS < 64 ? 2 * kShortRuns * kIt : pairs <= 512 ? kShortRuns * kIt : 0;
+  return pairs <= 256 ? 2 * kShortRuns * kIt : pairs <= 512 ? kShortRuns * kIt : 0;
 }
 // Every pair a wave touches costs it about a tile's time beyond its tiles (the
 // result goes through LDS, new queries and block ids arrive); the stream-K
@@ -705,7 +704,7 @@ struct ShortCut {
 template <int G, int BS, bool BF16, typename Sink>
 __device__ __forceinline__ void attend_run(const AttnArgs& a, Group g, const ShortCut& cut, int run,
                                            int lane, Sink&& sink) {
-  static_assert(short_tokens<BS>(1) <= 2 * kShortRuns * kIt, "a run is one or two tiles");
+  static_assert(short_tokens(1) <= 2 * kShortRuns * kIt, "a run is one or two tiles");
   const int r16 = lane & 15, q4 = lane >> 4;
   g.j0 = run * cut.per;
   g.j1 = min(g.nt, g.j0 + cut.per);
@@ -856,7 +855,7 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
     return nt > 0 ? (nt + kSegCost) * H : 0;
   };
   int total = 0;
-  const int at_most = short_tokens<BS>(int64_t(B) * H);
+  const int at_most = short_tokens(int64_t(B) * H);
   bool longer = at_most == 0;
   for (int c = b0; c < b1; c += 4) {
     int raw[4];
@@ -1049,16 +1048,20 @@ __global__ __launch_bounds__(kStreamThreads, 2) void attn_mfma_streamk(AttnArgs 
 // 10.2 / 10.3; 256 pairs 13.5 / 8.7, 17.9 / 13.7, 21.4 / 19.3; 512 pairs 17.5 /
 // 15.3, 24.1 / 24.0, 33.9 / 35.0; 1024 pairs of up to 256 24.1 / 24.7. At 1, 2 and
 // 8 heads the same within 5 %, at 16 more for the direct form (256 pairs 17.9 /
-// 9.9, 21.8 / 14.8). Block size 64, 32 pairs 9.9 / 7.3, up to 512 tokens 10.9 /
-// 11.0, 512 pairs 18.1 / 14.3 and 24.4 / 25.3.
-// Short pairs in a table too wide for it take a plan and, where their runs are
-// spread over the workgroups, the combine, but are cut the same way. Then, 4
+// 9.9, 21.8 / 14.8). Block size 64, 32 pairs 9.9 / 7.3, up to 512 tokens 10.6 /
+// 11.1, 256 pairs of up to 512 18.8 / 13.7, 512 pairs 18.1 / 14.3 and 24.4 / 25.3.
+// Short pairs that come to the stream-K form take a plan and, where their runs
+// are spread over the workgroups, the combine, but are cut the same way. Then, 4
 // heads, block size 16, stream-K's own ranges / one workgroup to a pair / the runs
 // spread: 8 pairs of up to 128 tokens 9.6 / 7.2 / 8.0, 256 9.6 / 9.2 / 8.1, 512 9.4
 // / 12.8 / 9.3; 64 pairs 10.6 / 7.9 / 8.7, 10.7 / 10.6 / 9.0, 11.3 / 14.8 / 10.7; 256
 // pairs 12.5 / 8.2 / 13.4, 13.5 / 11.4 / 14.5, 17.9 / 16.4 / 19.1; 512 pairs 15.1 /
 // 12.5, 17.5 / 18.7 and 24.1 / 28.1 -- hence one or two tiles a run up to 256 pairs
-// and one tile up to 512, runs spread up to one pair to two workgroups.
+// and one tile up to 512, runs spread up to one pair to two workgroups. At block
+// size 64 a batch of up to 64 pairs of 257-512 tokens does best with its runs
+// spread (8 pairs 9.2 / - / 8.3, 64 pairs 11.0 / - / 10.9; direct 9.0 and 12.0; all
+// of 470 tokens 10.1 / - / 8.4 and 13.3 / - / 11.4, direct 11.0 and 11.8), so it
+// does not take the direct form.
 template <int G, int BS, bool BF16>
 __global__ __launch_bounds__(kDirectThreads, 2) void attn_mfma_direct(AttnArgs a) {
   __shared__ Part<G> s_part[kShortRuns];
@@ -1232,8 +1235,9 @@ __global__ __launch_bounds__(kCombineWaves * 64) void attn_combine_streamk(AttnA
 template <int G, int BS, bool BF16>
 hipError_t launch_typed(const AttnArgs& a, hipStream_t stream) {
   const int64_t pairs = int64_t(a.batch) * a.kv_heads;
-  if (a.stream_k && short_tokens<BS>(pairs) > 0 &&
-      int64_t(a.max_blocks) * BS <= short_tokens<BS>(pairs)) {
+  const int64_t width = int64_t(a.max_blocks) * BS;
+  if (a.stream_k && short_tokens(pairs) > 0 && width <= short_tokens(pairs) &&
+      (BS < 64 || width <= kShortRuns * kIt || pairs > 64)) {
     hipLaunchKernelGGL((attn_mfma_direct<G, BS, BF16>), dim3(a.kv_heads, a.batch),
                        dim3(kDirectThreads), 0, stream, a);
     return hipGetLastError();

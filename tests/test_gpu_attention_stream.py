@@ -100,8 +100,9 @@ def test_partials_of_one_pair(ema, hq, others, tiles):
     (8, 8, 16, "f16", 8, 32), (32, 8, 16, "bf16", 64, 32), (4, 1, 32, "bf16", 256, 16),
     (16, 1, 64, "f16", 3, 4), (6, 3, 128, "bf16", 5, 2), (4, 2, 256, "bf16", 4, 1),
     (16, 8, 16, "f16", 64, 16),
-    # one past each line of the rule: 257 pairs, 513 pairs, 17 tiles, 9 tiles
-    (2, 1, 16, "bf16", 257, 32), (1, 1, 16, "f16", 513, 16), (4, 2, 32, "f16", 4, 17), (8, 1, 64, "bf16", 4, 5)])
+    (8, 1, 64, "bf16", 65, 8),
+    # one past each line of the rule: 257 pairs, 513 pairs, 17 tiles, 64 pairs of 9 tiles
+    (2, 1, 16, "bf16", 257, 32), (1, 1, 16, "f16", 513, 16), (1, 1, 64, "f16", 64, 5), (4, 2, 32, "f16", 4, 17), (8, 1, 64, "bf16", 4, 5)])
 def test_short_tables(ema, hq, hkv, bs, dtype, batch, width):
     """Both sides of the line between the direct and the stream-K form: lengths
     from 0 to the table's width, ids outside the pool, and the same outputs
@@ -202,9 +203,11 @@ def test_error_against_64_bits(ema, hq, hkv, bs, dtype, batch, lo, hi, bound):
     # pairs whose runs just have a slot each in the workspace, and one more
     (8, 1, 16, "bf16", 128, 300), (8, 1, 32, "bf16", 129, 512), (32, 2, 256, "bf16", 32, 256),
     (16, 1, 16, "f16", 65, 512),
-    (32, 8, 16, "bf16", 64, 256), (1, 1, 256, "bf16", 257, 256),
+    (32, 8, 16, "bf16", 64, 256), (1, 1, 256, "bf16", 257, 256), (8, 1, 64, "bf16", 64, 512),
+    (4, 1, 128, "f16", 65, 512), (2, 2, 256, "bf16", 100, 512),
     # past the rule by a pair or a token, and long
-    (2, 1, 16, "bf16", 257, 512), (2, 1, 32, "f16", 300, 257), (2, 1, 64, "f16", 513, 256), (4, 2, 32, "f16", 9, 513), (8, 1, 64, "bf16", 4, 257),
+    (2, 1, 16, "bf16", 257, 512), (2, 1, 32, "f16", 300, 257), (2, 1, 64, "f16", 513, 256),
+    (4, 2, 32, "f16", 9, 513), (8, 1, 64, "bf16", 4, 513),
     (16, 4, 16, "bf16", 30, 3000)])
 def test_wider_tables_give_the_same_bits(ema, hq, hkv, bs, dtype, batch, longest):
     """One batch through tables just wide enough and wider ones, on both sides
