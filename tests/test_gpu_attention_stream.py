@@ -99,10 +99,10 @@ def test_partials_of_one_pair(ema, hq, others, tiles):
 @pytest.mark.parametrize("hq,hkv,bs,dtype,batch,width", [
     (8, 8, 16, "f16", 8, 32), (32, 8, 16, "bf16", 64, 32), (4, 1, 32, "bf16", 256, 16),
     (16, 1, 64, "f16", 3, 4), (6, 3, 128, "bf16", 5, 2), (4, 2, 256, "bf16", 4, 1),
-    (16, 8, 16, "f16", 64, 16),
-    (8, 1, 64, "bf16", 65, 8),
+    (16, 8, 16, "f16", 64, 16), (8, 1, 64, "bf16", 65, 8),
     # one past each line of the rule: 257 pairs, 513 pairs, 17 tiles, 64 pairs of 9 tiles
-    (2, 1, 16, "bf16", 257, 32), (1, 1, 16, "f16", 513, 16), (1, 1, 64, "f16", 64, 5), (4, 2, 32, "f16", 4, 17), (8, 1, 64, "bf16", 4, 5)])
+    (2, 1, 16, "bf16", 257, 32), (1, 1, 16, "f16", 513, 16), (1, 1, 64, "f16", 64, 5),
+    (4, 2, 32, "f16", 4, 17), (8, 1, 64, "bf16", 4, 5)])
 def test_short_tables(ema, hq, hkv, bs, dtype, batch, width):
     """Both sides of the line between the direct and the stream-K form: lengths
     from 0 to the table's width, ids outside the pool, and the same outputs
